@@ -164,17 +164,15 @@ struct FastAttnArgs {
     int nsplit;                 // position splits per (row, KV head): 1 = one block merges everything
     int split_pages;            // pages per split (split k covers pages [k, k+1) * split_pages of a row)
     float* split_part;          // nsplit > 1: partials [B][Hq][nsplit][hd + 2] (m, l, O), merged by a second launch
+    int n_cu;                   // compute units of the device (chooses the block order)
+    bool longest_first;         // blocks in order of decreasing context (set by the launch)
 };
 hipError_t launch_fast_attention(const FastAttnArgs& a, hipStream_t s);
 // position splits of the fast attention for `rows` rows: 1 when the (row, KV head) blocks
 // fill the device; else enough (row, KV head, split) blocks to fill it (at least 16 pages of
 // capacity per split) and no split longer than 64 pages of capacity, so that rows of ragged
 // lengths give blocks of bounded work
-// (row, KV head) units: `n_kv_heads` is the KV-head count times the head groups
 int fast_attn_splits(int rows, int n_kv_heads, int max_pages_per_row, int n_cu, int cap);
-// blocks per (row, KV head, split): query-head groups of at most 4 (more than 4 heads per
-// block do not fit two blocks per CU in registers)
-int fast_attn_head_groups(int n_q_heads, int n_kv_heads);
 
 // ---------------------------------------------------------------- gate / repair / misc
 // top-1 / top-2 of B <= 256 logit rows in two launches (vocabulary slices, then a
