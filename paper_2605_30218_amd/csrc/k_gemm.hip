@@ -6,13 +6,12 @@
 // output features; a wave owns 16 of them for all rows (the activation chunk staged in
 // LDS serves all of the block's waves).  The block walks its K range in chunks of KC,
 // requesting later chunks while the MFMAs of the current one run.  Two operand paths:
-//  * K % 128 == 0 and up to 128 rows (128-element chunks): both operands go through
-//    LDS by direct-to-LDS loads -- each wave's weights through its own ring of DEPTH
-//    stages (two chunks ahead up to 64 rows, one above), the activations through a
-//    block-wide double buffer --
+//  * K % 128 == 0 and up to 64 rows (128-element chunks): both operands go through
+//    LDS by direct-to-LDS loads -- each wave's weights through its own ring of three
+//    stages (two chunks ahead), the activations through a block-wide double buffer --
 //    in a swizzled layout whose loads read each row's chunk as one contiguous run and
 //    whose MFMA fragment reads are free of bank conflicts (see issue_w_lds).
-//  * otherwise: weights straight from HBM into MFMA B-operand registers (lane (j, q)
+//  * otherwise (above 64 rows only K % 128 != 0: k_gemm_wide.hip takes the rest): weights straight from HBM into MFMA B-operand registers (lane (j, q)
 //    loads W[n+j][k+8q .. k+8q+7], 16 rows x 64 contiguous bytes per k step of 16
 //    features) in a ping-pong register pair, the activations staged through a
 //    double-buffered, padded LDS tile.  Loads complete in order, so staging the
@@ -53,8 +52,8 @@ struct GemmShape {
     static constexpr int XLD = (ROWS * GPR + GM_THREADS - 1) / GM_THREADS;  // staging loads per thread per chunk
     // 128-element chunks take the weights through a per-wave LDS ring of DEPTH stages and
     // the activations through a double buffer (direct-to-LDS loads; 160 KiB of LDS)
-    static constexpr bool LDSW = KC == 128;  // (with K % 128 == 0, chosen at launch)
-    static constexpr int DEPTH = MT <= 4 ? 3 : 2;
+    static constexpr bool LDSW = MT <= 4;  // (with K % 128 == 0, chosen at launch)
+    static constexpr int DEPTH = 3;
 };
 
 template <int EPI>
@@ -132,9 +131,10 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 __device__ __forceinline__ int piece_slot(int j, int G) { return 64 * (j >> 2) + 16 * (j & 3) + (G ^ j); }
 
-// load st of a 16-row block whose row j starts at rowp(j)
-__device__ __forceinline__ void issue_block_load(const uint16_t* src, uint4* block, int st, int lane) {
-    __builtin_amdgcn_global_load_lds(src, block + 64 * st, 16, 0, 0);
+// load st of a 16-row block (AUX: cache policy)
+template <int AUX>
+__device__ __forceinline__ void issue_block_load(const uint16_t* src, uint4* block, int st) {
+    __builtin_amdgcn_global_load_lds(src, block + 64 * st, 16, 0, AUX);
 }
 
 __device__ __forceinline__ void issue_w_lds(const uint16_t* tile, int K, int kc, int lane, uint4* stage) {
@@ -142,7 +142,7 @@ __device__ __forceinline__ void issue_w_lds(const uint16_t* tile, int K, int kc,
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
         const int j = 4 * st + r;
-        issue_block_load(tile + (size_t)j * K + kc + 8 * (g ^ j), stage, st, lane);
+        issue_block_load<0>(tile + (size_t)j * K + kc + 8 * (g ^ j), stage, st);
     }
 }
 
@@ -160,7 +160,7 @@ __device__ __forceinline__ void issue_x_lds(const FastGemmArgs& a, int kc, int w
     for (int t = 0; t < XI; ++t) {
         const int ii = (wave * XI + t) % NI, bb = ii >> 2, st = ii & 3;
         const int j = 4 * st + r, row = min(16 * bb + j, a.M - 1);
-        issue_block_load(a.X + (size_t)row * a.K + kc + 8 * (g ^ j), xt + 256 * bb, st, lane);
+        issue_block_load<0>(a.X + (size_t)row * a.K + kc + 8 * (g ^ j), xt + 256 * bb, st);
     }
 }
 
@@ -178,16 +178,11 @@ __device__ __forceinline__ void lds_wait_frags(u32x4_t (&wv)[2], u32x4_t (&xv)[2
     } else if constexpr (MT == 2) {
         asm volatile("s_waitcnt lgkmcnt(0)"
                      : "+v"(wv[0]), "+v"(wv[1]), "+v"(xv[0][0]), "+v"(xv[0][1]), "+v"(xv[1][0]), "+v"(xv[1][1]) : : "memory");
-    } else if constexpr (MT == 4) {
+    } else {
+        static_assert(MT == 4, "tile count");
         asm volatile("s_waitcnt lgkmcnt(0)"
                      : "+v"(wv[0]), "+v"(wv[1]), "+v"(xv[0][0]), "+v"(xv[0][1]), "+v"(xv[0][2]), "+v"(xv[0][3]),
                        "+v"(xv[1][0]), "+v"(xv[1][1]), "+v"(xv[1][2]), "+v"(xv[1][3]) : : "memory");
-    } else {
-        static_assert(MT == 8, "tile count");
-        asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+v"(wv[0]), "+v"(wv[1]), "+v"(xv[0][0]), "+v"(xv[0][1]), "+v"(xv[0][2]), "+v"(xv[0][3]),
-                       "+v"(xv[0][4]), "+v"(xv[0][5]), "+v"(xv[0][6]), "+v"(xv[0][7]), "+v"(xv[1][0]), "+v"(xv[1][1]),
-                       "+v"(xv[1][2]), "+v"(xv[1][3]), "+v"(xv[1][4]), "+v"(xv[1][5]), "+v"(xv[1][6]), "+v"(xv[1][7]) : : "memory");
     }
 }
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
@@ -484,14 +479,14 @@ static int mt_for(int M) {
 constexpr int GM_FT = 1;
 constexpr int LDS_PER_CU = 160 * 1024;
 
-// whole 128-element chunks take both operands through LDS by direct-to-LDS loads
-static bool lds_path(int M, int K) { return gemm_kc(mt_for(M)) == 128 && K % 128 == 0; }
+// up to 64 rows, whole 128-element chunks take both operands through LDS by direct-to-LDS loads
+// (above 64 rows they go to k_gemm_wide.hip)
+static bool lds_path(int M, int K) { return M <= 64 && K % 128 == 0; }
 
 // blocks of NW waves that fit on one CU at once on the direct-to-LDS path (its LDS: the
 // weight ring of DEPTH x NW stages of 4 KiB and the activation double buffer of 2 x MT x 4 KiB)
 static int lds_slots(int MT, int NW) {
-    const int depth = MT <= 4 ? 3 : 2;
-    const int bytes = (depth * NW + 2 * MT) * 4096;
+    const int bytes = (3 * NW + 2 * MT) * 4096;
     return LDS_PER_CU / bytes > 1 ? LDS_PER_CU / bytes : 1;
 }
 
@@ -552,16 +547,18 @@ static int max_splits(int M, int K) {
     return S < 1 ? 1 : S;
 }
 
-bool fast_gemm_lds_path(int M, int K) { return lds_path(M, K); }
+bool fast_gemm_lds_path(int M, int K) { return lds_path(M, K) || wide_gemm_takes(M, K); }
 
 // waves per block for a launch with S splits
 static int fast_gemm_waves(int M, int N, int K, int S, int n_cu) {
+    if (wide_gemm_takes(M, K)) return wide_gemm_waves(M, N, K, S, n_cu);
     if (!lds_path(M, K)) return GM_NW;
     return lds_cost(M, N, K, S, 4, n_cu) < lds_cost(M, N, K, S, 8, n_cu) ? 4 : 8;
 }
 
 int fast_gemm_splits(int M, int N, int K, int n_cu) {
     const int Smax = max_splits(M, K);
+    if (wide_gemm_takes(M, K)) return wide_gemm_splits(M, N, K, Smax, n_cu);
     if (lds_path(M, K)) {
         // the cheapest (splits, waves) pair; the launch picks the waves again for its S
         int best_S = 1;
@@ -582,6 +579,7 @@ int fast_gemm_splits(int M, int N, int K, int n_cu) {
 }
 
 int fast_gemm_blocks(int M, int N, int K, int n_cu) {
+    if (wide_gemm_takes(M, K)) return wide_gemm_blocks(M, N, K, n_cu);
     const int NW = fast_gemm_waves(M, N, K, 1, n_cu);
     return (N + 16 * NW * GM_FT - 1) / (16 * NW * GM_FT);
 }
@@ -594,17 +592,17 @@ void fast_gemm_config(int M, int N, int K, int n_cu, int* S, int* waves) {
 template <int MT, int NW, int FT, int EPI>
 static void launch_epi(const FastGemmArgs& a, dim3 g, hipStream_t s) {
     if constexpr (EPI == FEPI_SWIGLU) {  // direct-to-LDS path only (checked by the launcher)
-        if constexpr (gemm_kc(MT) == 128)
+        if constexpr (GemmShape<MT>::LDSW)
             hipLaunchKernelGGL((fast_gemm_kernel<MT, NW, FT, EPI, true>), g, dim3(64 * NW), 0, s, a);
         return;
     }
     if constexpr (NW == GM_NW) {
-        if (!(gemm_kc(MT) == 128 && a.K % 128 == 0)) {
+        if (!lds_path(a.M, a.K)) {
             hipLaunchKernelGGL((fast_gemm_kernel<MT, NW, FT, EPI, false>), g, dim3(64 * NW), 0, s, a);
             return;
         }
     }
-    if constexpr (gemm_kc(MT) == 128)
+    if constexpr (GemmShape<MT>::LDSW)
         hipLaunchKernelGGL((fast_gemm_kernel<MT, NW, FT, EPI, true>), g, dim3(64 * NW), 0, s, a);
 }
 
@@ -623,7 +621,7 @@ template <int MT>
 static void launch_mt(const FastGemmArgs& a, int epi, int NW, hipStream_t s) {
     const int per_block = epi == FEPI_SWIGLU ? 16 * (NW / 2) : 16 * NW * GM_FT;  // outputs per block
     dim3 g((a.N + per_block - 1) / per_block, a.S);
-    if constexpr (gemm_kc(MT) == 128) {
+    if constexpr (GemmShape<MT>::LDSW) {
         if (NW == 4) return launch_ft<MT, 4, GM_FT>(a, epi, g, s);
     }
     launch_ft<MT, GM_NW, GM_FT>(a, epi, g, s);
@@ -633,8 +631,9 @@ hipError_t launch_fast_gemm(const FastGemmArgs& a, int epi, hipStream_t s) {
     if (a.M <= 0 || a.N <= 0) return hipSuccess;
     if (a.K < 8 || a.K % 8 || a.N % 16) return hipErrorInvalidValue;
     if (epi != FEPI_PART && a.S != 1) return hipErrorInvalidValue;  // only partial tiles may be split
-    if (epi == FEPI_SWIGLU && (a.S != 1 || !lds_path(a.M, a.K) || a.Nseg[0] != a.N || a.Nseg[1] != a.N))
+    if (epi == FEPI_SWIGLU && (a.S != 1 || !fast_gemm_lds_path(a.M, a.K) || a.Nseg[0] != a.N || a.Nseg[1] != a.N))
         return hipErrorInvalidValue;
+    if (wide_gemm_takes(a.M, a.K)) return launch_wide_gemm(a, epi, s);
     // a SwiGLU launch streams the gate and the up rows: 2N weight rows
     const int NW = fast_gemm_waves(a.M, epi == FEPI_SWIGLU ? 2 * a.N : a.N, a.K, a.S, a.n_cu > 0 ? a.n_cu : 256);
     switch (mt_for(a.M)) {

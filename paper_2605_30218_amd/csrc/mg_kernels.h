@@ -104,6 +104,14 @@ void fast_gemm_config(int M, int N, int K, int n_cu, int* S, int* waves);
 // whether M rows of a K-long projection take the direct-to-LDS operand path
 bool fast_gemm_lds_path(int M, int K);
 
+// batches above 64 rows with K % 128 == 0 (k_gemm_wide.hip): whether M rows take it, its split count
+// (at most S_max), waves per block and feature blocks of an unsplit launch
+bool wide_gemm_takes(int M, int K);
+int wide_gemm_splits(int M, int N, int K, int S_max, int n_cu);
+int wide_gemm_waves(int M, int N, int K, int S, int n_cu);
+int wide_gemm_blocks(int M, int N, int K, int n_cu);
+hipError_t launch_wide_gemm(const FastGemmArgs& a, int epi, hipStream_t s);
+
 // fast-path consumers of split partial tiles
 // x[r] = bf16(x[r] + bf16(sum_s part[s][r])) (skipped when part == NULL; with embed != NULL,
 // x[r] = embed[token of r] instead), then h[r] = bf16((x * rms^-1) * gamma)

@@ -1,0 +1,62 @@
+"""The fast path's projection above 64 rows (K % 128 == 0) at the edges of its tiles: row counts
+around the 64-row blocks, feature counts around 16-feature tiles and narrow blocks, one and
+several 128-element units of K, split K, and the SwiGLU and top-2 epilogues against batches
+small enough for the other kernel (the same order of every sum, so the same bits)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import mgo
+from paper_2605_30218_amd import mg, synth
+
+from _gpu_common import Pair, dev_i32, u16
+
+pytestmark = pytest.mark.gpu
+
+
+def to_dev(a):
+    return torch.as_tensor(a.view(np.int16)).to("cuda")
+
+
+@pytest.mark.parametrize("n", [65, 80, 127, 128, 129, 192, 193, 251, 256])
+@pytest.mark.parametrize("N,K", [(16, 128), (48, 256), (4112, 384), (9232, 512), (37888, 256), (112, 8192), (2064, 4480)])
+def test_small_integers_exact(n, N, K):
+    """Every partial sum is an integer below 2^24: any order gives the exact sum."""
+    X = synth.small_int_bf16((n, K), seed=n)
+    W = synth.small_int_bf16((N, K), seed=N)
+    Y = mg.op_linear(False, to_dev(X), to_dev(W)).cpu().numpy()
+    ref = (torch.as_tensor(mgo.f32_from_bf16(X)).cuda().double() @ torch.as_tensor(mgo.f32_from_bf16(W)).cuda().double().T)
+    np.testing.assert_array_equal(Y, ref.cpu().numpy().astype(np.float32))
+
+
+@pytest.mark.parametrize("F", [128, 400, 1024])
+def test_matrix_core_verifier_bits_across_the_kernels(F):
+    """The matrix-core verifier's logits, tokens and columns for n rows at once are those of the
+    rows in groups of 20 (the kernel for up to 64 rows), with the logits and without."""
+    s = synth.ModelShape("wide", 2, 384, 6, 2, 64, F, 1040, True, 1e4, 1e-5)
+    B = 201
+    pair = Pair(s, max_batch=B, ctx_cap=48, seed=F)
+    e = pair.eng
+    synth.fill_synthetic_kv(e.kv_view(), np.arange(pair.n_pages), seed=1)
+    rng = np.random.RandomState(F)
+    tok, pos = dev_i32(rng.randint(0, s.vocab, B)), dev_i32(rng.randint(0, 48, B))
+    pt = dev_i32(pair.pt)
+
+    def run(rows, logits):
+        n = len(rows)
+        lg = torch.empty((n, s.vocab), device="cuda") if logits else None
+        vt = torch.empty(n, dtype=torch.int32, device="cuda")
+        vc = torch.empty((n, e.col_elems), dtype=torch.int16, device="cuda")
+        e.verify_rows_mfma(n, dev_i32(rows), tok, pos, pt, lg, vt, vc)
+        torch.cuda.synchronize()
+        return (lg.cpu().numpy().view(np.uint32) if logits else np.zeros((n, 1))), vt.cpu().numpy(), u16(vc)
+
+    parts = [run(np.arange(r, min(r + 20, B)), True) for r in range(0, B, 20)]
+    want = [np.concatenate([p[k] for p in parts]) for k in range(3)]
+    for n in (65, 100, 130, B):
+        for logits in (True, False):
+            got = run(np.arange(n), logits)
+            if logits:
+                np.testing.assert_array_equal(got[0], want[0][:n])
+            np.testing.assert_array_equal(got[1], want[1][:n])
+            np.testing.assert_array_equal(got[2], want[2][:n])
