@@ -131,7 +131,8 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 __device__ __forceinline__ int piece_slot(int j, int G) { return 64 * (j >> 2) + 16 * (j & 3) + (G ^ j); }
 
-// load st of a 16-row block (AUX: cache policy)
+// load st of a 16-row block (AUX: cache policy; the weights are streamed: gate/up at 64 rows 46 us with
+// the nt policy, 51 without)
 template <int AUX>
 __device__ __forceinline__ void issue_block_load(const uint16_t* src, uint4* block, int st) {
     __builtin_amdgcn_global_load_lds(src, block + 64 * st, 16, 0, AUX);
@@ -142,7 +143,7 @@ __device__ __forceinline__ void issue_w_lds(const uint16_t* tile, int K, int kc,
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
         const int j = 4 * st + r;
-        issue_block_load<0>(tile + (size_t)j * K + kc + 8 * (g ^ j), stage, st);
+        issue_block_load<MG_AUX_NT>(tile + (size_t)j * K + kc + 8 * (g ^ j), stage, st);
     }
 }
 

@@ -102,12 +102,16 @@ __device__ __forceinline__ void gemv_store_x(float4 (*xs)[2][64], int wave, int 
     }
 }
 
-// weights of group g (clamped to the last group) of the J feature rows
+// weights of group g (clamped to the last group) of the J feature rows, streamed ("nt" policy: at 5
+// rows the 4096 x 14336 down projection 27.8 us against 30.6, O 11.6 against 12.5)
 template <int J>
 __device__ __forceinline__ void gemv_load_w(const uint16_t* const (&wrow)[J], int g, int G, uint4 (&w)[J]) {
     const int gc = min(g, G - 1);
 #pragma unroll
-    for (int jj = 0; jj < J; ++jj) w[jj] = *reinterpret_cast<const uint4*>(wrow[jj] + (size_t)gc * 8);
+    for (int jj = 0; jj < J; ++jj) {
+        using u4 = uint32_t __attribute__((ext_vector_type(4)));
+        w[jj] = __builtin_bit_cast(uint4, __builtin_nontemporal_load(reinterpret_cast<const u4*>(wrow[jj] + (size_t)gc * 8)));
+    }
 }
 
 // this lane's group of one chunk for every live row: sequential fma in element order
