@@ -493,9 +493,11 @@ static int lds_slots(int MT, int NW) {
 
 // Launch cost of NW-wave blocks with S splits on the direct-to-LDS path.  Launches whose
 // blocks are all resident at once (one round) come first, compared by the weight bytes
-// of the busiest CU, then the resident waves (more requests in flight), the split count
-// (partial-tile traffic), and a preference for 4-wave blocks at up to 16 rows (measured
-// faster there) and for 8-wave blocks above.  Launches of several rounds already have
+// of the busiest CU, then (above 16 rows) the resident waves (more requests in flight), the split
+// count (partial-tile traffic), and a preference for 4-wave blocks at up to 16 rows (measured
+// faster there) and for 8-wave blocks above.  Up to 16 rows the split count comes before the waves: half
+// the partial tiles and 256 blocks of 4 waves instead of 512 take the 4096 x 4096 projection
+// from 12.6 to 10.9 us at 16 rows, 11.8 to 10.5 at one (4096 x 14336: 25.4 to 23.4, 24.3 to 22.8).  Launches of several rounds already have
 // blocks enough: fewest splits first, then the block size.  A block streams 16 NW
 // features over its split's 128-element units (splits differ by at most one unit).
 struct LaunchCost {
@@ -503,6 +505,7 @@ struct LaunchCost {
     long cu_bytes;
     long waves;
     int S, pref;
+    bool few_rows;
     bool operator<(const LaunchCost& o) const {
         if ((rounds == 1) != (o.rounds == 1)) return rounds == 1;
         if (rounds != 1) {
@@ -511,6 +514,7 @@ struct LaunchCost {
             return cu_bytes < o.cu_bytes;
         }
         if (cu_bytes != o.cu_bytes) return cu_bytes < o.cu_bytes;
+        if (few_rows && S != o.S) return S < o.S;
         if (waves != o.waves) return waves > o.waves;
         if (S != o.S) return S < o.S;
         return pref < o.pref;
@@ -527,6 +531,7 @@ static LaunchCost lds_cost(int M, int N, int K, int S, int NW, int n_cu) {
     c.cu_bytes = per_cu * split_units * 128 * 16 * NW * GM_FT * 2;
     c.waves = (blocks < (long)n_cu * slots ? blocks : (long)n_cu * slots) * NW;
     c.S = S;
+    c.few_rows = M <= 16;
     // several rounds: two 4-wave blocks per CU overlap one block's start with the other's
     // stream (measured on the 128256-feature LM head); one round: as stated above
     if (c.rounds != 1) c.pref = (NW == 4) == (lds_slots(MT, 4) >= 2) ? 0 : 1;
@@ -547,6 +552,8 @@ static int max_splits(int M, int K) {
     if (S > 32) S = 32;
     return S < 1 ? 1 : S;
 }
+
+static bool few_blocks(int epi, int M, int N, int K, int n_cu);
 
 bool fast_gemm_lds_path(int M, int K) { return lds_path(M, K) || wide_gemm_takes(M, K); }
 
@@ -580,7 +587,7 @@ int fast_gemm_splits(int M, int N, int K, int n_cu) {
 }
 
 int fast_gemm_blocks(int M, int N, int K, int n_cu) {
-    if (wide_gemm_takes(M, K)) return wide_gemm_blocks(M, N, K, n_cu);
+    if (wide_gemm_takes(M, K) || few_blocks(FEPI_TOP2, M, N, K, n_cu)) return wide_gemm_blocks(M, N, K, n_cu);
     const int NW = fast_gemm_waves(M, N, K, 1, n_cu);
     return (N + 16 * NW * GM_FT - 1) / (16 * NW * GM_FT);
 }
@@ -618,6 +625,13 @@ static void launch_ft(const FastGemmArgs& a, int epi, dim3 g, hipStream_t s) {
     }
 }
 
+// An unsplit output (the LM head) of 17 to 64 rows and so few features that 4-wave blocks leave
+// half of the CUs idle goes to the smaller tiles of k_gemm_wide.hip (4096 features at 64 rows: 17.8 us
+// in 256 blocks against 22.2 in 64; up to 16 rows the two are equal)
+static bool few_blocks(int epi, int M, int N, int K, int n_cu) {
+    return (epi == FEPI_F32 || epi == FEPI_TOP2) && M > 16 && lds_path(M, K) && (N + 63) / 64 <= n_cu / 2;
+}
+
 template <int MT>
 static void launch_mt(const FastGemmArgs& a, int epi, int NW, hipStream_t s) {
     const int per_block = epi == FEPI_SWIGLU ? 16 * (NW / 2) : 16 * NW * GM_FT;  // outputs per block
@@ -634,7 +648,8 @@ hipError_t launch_fast_gemm(const FastGemmArgs& a, int epi, hipStream_t s) {
     if (epi != FEPI_PART && a.S != 1) return hipErrorInvalidValue;  // only partial tiles may be split
     if (epi == FEPI_SWIGLU && (a.S != 1 || !fast_gemm_lds_path(a.M, a.K) || a.Nseg[0] != a.N || a.Nseg[1] != a.N))
         return hipErrorInvalidValue;
-    if (wide_gemm_takes(a.M, a.K)) return launch_wide_gemm(a, epi, s);
+    if (wide_gemm_takes(a.M, a.K) || few_blocks(epi, a.M, a.N, a.K, a.n_cu > 0 ? a.n_cu : 256))
+        return launch_wide_gemm(a, epi, s);
     // a SwiGLU launch streams the gate and the up rows: 2N weight rows
     const int NW = fast_gemm_waves(a.M, epi == FEPI_SWIGLU ? 2 * a.N : a.N, a.K, a.S, a.n_cu > 0 ? a.n_cu : 256);
     switch (mt_for(a.M)) {

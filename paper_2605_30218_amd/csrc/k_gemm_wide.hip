@@ -1,6 +1,7 @@
-// k_gemm_wide.hip -- the fast path's projection for batches above 64 rows.
+// k_gemm_wide.hip -- the fast path's projection for batches above 64 rows (and, from 17 rows, for
+// unsplit outputs of few features).
 //
-// Y[M][N] = X[M][K] * W[N][K]^T with v_mfma_f32_16x16x32_bf16, 64 < M <= 256, K % 128 == 0.
+// Y[M][N] = X[M][K] * W[N][K]^T with v_mfma_f32_16x16x32_bf16, M <= 256, K % 128 == 0.
 // With one 16-feature tile per wave (k_gemm.hip) every wave reads the whole activation chunk
 // from LDS for 16 features, and above 64 rows those reads, not the weight stream, set the
 // time.  Here a block owns BM = 64 MT rows x BN = 16 NT WN features as 4 x WN waves of MT x NT
@@ -348,7 +349,7 @@ static void launch_wide_mt(const FastGemmArgs& a, int epi, const WideLaunch& c, 
 }
 
 hipError_t launch_wide_gemm(const FastGemmArgs& a, int epi, hipStream_t s) {
-    if (!wide_gemm_takes(a.M, a.K)) return hipErrorInvalidValue;
+    if (a.M < 1 || a.M > 256 || a.K % 128) return hipErrorInvalidValue;
     // a SwiGLU launch streams the gate and the up rows: 2N weight rows
     const bool pairs = epi == FEPI_SWIGLU;
     const WideLaunch c = wide_choose(a.M, pairs ? 2 * a.N : a.N, a.K, a.S, pairs, a.n_cu > 0 ? a.n_cu : 256);
