@@ -397,23 +397,6 @@ static void launch_canon_g(const AttnArgs& a, int G, dim3 g1, bool many, hipStre
     }
 }
 
-// item i: tab[i][0] = its position p, tab[i][1 + k] = its row's page of slot min(k, p / 16)
-__global__ __launch_bounds__(256) void item_table_kernel(Items it, int mpr, int32_t* __restrict__ tab) {
-    const int i = blockIdx.x;
-    if (i >= items_n(it)) return;
-    const int r = items_row(it, i), p = items_pos(it, i);
-    const int32_t* ptab = it.page_table + (size_t)r * mpr;
-    int32_t* tb = tab + (size_t)i * (1 + mpr);
-    if (threadIdx.x == 0) tb[0] = p;
-    for (int k = threadIdx.x; k < mpr; k += 256) tb[1 + k] = ptab[min(k, p >> 4)];
-}
-
-hipError_t launch_item_table(const Items& it, const ModelDims& m, int32_t* itab, hipStream_t s) {
-    if (it.n_host <= 0) return hipSuccess;
-    hipLaunchKernelGGL(item_table_kernel, dim3(it.n_host), dim3(256), 0, s, it, m.max_pages_per_row, itab);
-    return hipGetLastError();
-}
-
 hipError_t launch_attention(const AttnArgs& a, int canon, hipStream_t s) {
     const int n = a.it.n_host;
     if (n <= 0) return hipSuccess;

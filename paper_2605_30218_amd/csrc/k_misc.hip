@@ -1,4 +1,4 @@
-// k_misc.hip -- embedding gather, RMSNorm, RoPE + K/V placement, SwiGLU, the
+// k_misc.hip -- RMSNorm (with the item table and embedding gather of a forward's start), RoPE + K/V placement, SwiGLU, the
 // top-1/top-2 margin gate, the K/V column repair, step bookkeeping, numerics probes.
 #include "mg_device.h"
 #include "mg_kernels.h"
@@ -6,51 +6,41 @@
 
 namespace mg {
 
-// ------------------------------------------------------------------ embedding
-// x[i][:] = embed[token of item i][:]
-__global__ __launch_bounds__(256) void embed_kernel(Items it, const uint16_t* __restrict__ E, int d,
-                                                    uint16_t* __restrict__ x) {
-    const int i = blockIdx.x;
-    if (i >= items_n(it)) return;
-    const int tok = items_tok(it, i);
-    const uint4* src = reinterpret_cast<const uint4*>(E + (size_t)tok * d);
-    uint4* dst = reinterpret_cast<uint4*>(x + (size_t)i * d);
-    for (int t = threadIdx.x; t < d / 8; t += blockDim.x) dst[t] = src[t];
-}
-
-hipError_t launch_embed(const Items& it, const uint16_t* embed, int d, uint16_t* x, hipStream_t s) {
-    if (it.n_host <= 0) return hipSuccess;
-    hipLaunchKernelGGL(embed_kernel, dim3(it.n_host), dim3(256), 0, s, it, embed, d, x);
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------------------ RMSNorm
-// One wave per row.  ss = CDOT(x, x) (lane l owns groups l, l+64, ...; fma in
-// element order; xor butterfly), m = ss / d, r = 1 / sqrt(m + eps),
-// y_i = bf16((x_i * r) * gamma_i).  Used by both paths (it is batch-invariant).
+// ss = CDOT(x, x) (lane l owns groups l, l+64, ...; fma in element order; xor butterfly),
+// m = ss / d, r = 1 / sqrt(m + eps), y_i = bf16((x_i * r) * gamma_i).
+// The order of the sum leaves one wave per row for it, and a lone wave is bound by its own
+// instruction stream (a vector instruction every 4 cycles: 8 per value for the output alone).  So
+// four waves take a row: each forms the whole sum for itself (no exchange, no barrier) and writes
+// every fourth 64-group slice of the output.  Against one wave per row: 4.9 and 6.6 us at 5 rows of
+// 4096 values, 4.9 and 7.6 at 18 of 5120, 5.0 and 7.1 at 64 and 6.5 and 8.0 at 1000 of 4096.
 constexpr int RMS_MAXG = 16;  // groups of 8 per lane: d <= 8192
+constexpr int RMS_NW = 4;     // waves per row
 
-__global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ g,
-                                                      RowCount rc, int d, float eps, uint16_t* __restrict__ y) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + wave;
-    if (row >= rc.get()) return;
-    const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)row * d);
+// one row by this wave: src -> y (and xout, if not NULL, gets a copy of src), slices part, part + RMS_NW, ...
+__device__ __forceinline__ void rmsnorm_row(const uint16_t* src, const uint16_t* gamma, int d, float eps, int lane,
+                                            int part, uint16_t* xout, uint16_t* y) {
+    const uint4* xr = reinterpret_cast<const uint4*>(src);
+    const uint4* gr = reinterpret_cast<const uint4*>(gamma);
     const int G = d >> 3;
-    // the lane's groups lane, lane+64, ... are loaded together and kept in registers
-    // gamma is requested with x, so the block waits for memory once
-    const uint4* gr = reinterpret_cast<const uint4*>(g);
-    uint4 xv[RMS_MAXG], gv[RMS_MAXG];
+    // everything is requested together, so the wave waits for memory once (the wave's own slices
+    // twice: a register array indexed by `part` would live in scratch memory)
+    constexpr int NO = RMS_MAXG / RMS_NW;
+    uint4 xv[RMS_MAXG], xo[NO], gv[NO];
 #pragma unroll
-    for (int k = 0; k < RMS_MAXG; ++k) {
-        const int gi = lane + 64 * k;
-        xv[k] = gi < G ? xr[gi] : make_uint4(0, 0, 0, 0);
-        gv[k] = gi < G ? gr[gi] : make_uint4(0, 0, 0, 0);
-    }
+    for (int k = 0; k < RMS_MAXG; ++k)
+        if (64 * k < G) xv[k] = xr[min(lane + 64 * k, G - 1)];
+#pragma unroll
+    for (int k = 0; k < NO; ++k)
+        if (64 * RMS_NW * k < G) {
+            const int gi = min(lane + 64 * (RMS_NW * k + part), G - 1);
+            xo[k] = xr[gi];
+            gv[k] = gr[gi];
+        }
     float a = 0.0f;
 #pragma unroll
     for (int k = 0; k < RMS_MAXG; ++k) {
-        if (lane + 64 * k < G) {
+        if (64 * k < G && lane + 64 * k < G) {
             const uint4 v = xv[k];
             const float e[8] = {bf_lo(v.x), bf_hi(v.x), bf_lo(v.y), bf_hi(v.y),
                                 bf_lo(v.z), bf_hi(v.z), bf_lo(v.w), bf_hi(v.w)};
@@ -61,20 +51,29 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const uint16_t* __restrict
     const float ss = butterfly_sum(a);
     const float m = ieee_div(ss, (float)d);
     const float r = ieee_div(1.0f, ieee_sqrt(m + eps));
-    uint4* yr = reinterpret_cast<uint4*>(y + (size_t)row * d);
+    uint4* yr = reinterpret_cast<uint4*>(y);
 #pragma unroll
-    for (int k = 0; k < RMS_MAXG; ++k) {
-        const int gi = lane + 64 * k;
-        if (gi < G) {
-            const uint4 v = xv[k], w = gv[k];
+    for (int k = 0; k < NO; ++k) {
+        const int gi = lane + 64 * (RMS_NW * k + part);
+        if (64 * RMS_NW * k < G && gi < G) {
+            const uint4 v = xo[k], w = gv[k];
             uint4 o;
             o.x = pack_bf2((bf_lo(v.x) * r) * bf_lo(w.x), (bf_hi(v.x) * r) * bf_hi(w.x));
             o.y = pack_bf2((bf_lo(v.y) * r) * bf_lo(w.y), (bf_hi(v.y) * r) * bf_hi(w.y));
             o.z = pack_bf2((bf_lo(v.z) * r) * bf_lo(w.z), (bf_hi(v.z) * r) * bf_hi(w.z));
             o.w = pack_bf2((bf_lo(v.w) * r) * bf_lo(w.w), (bf_hi(v.w) * r) * bf_hi(w.w));
             yr[gi] = o;
+            if (xout) reinterpret_cast<uint4*>(xout)[gi] = v;
         }
     }
+}
+
+__global__ __launch_bounds__(64 * RMS_NW) void rmsnorm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ g,
+                                                              RowCount rc, int d, float eps, uint16_t* __restrict__ y) {
+    const int row = blockIdx.x;
+    if (row >= rc.get()) return;
+    rmsnorm_row(x + (size_t)row * d, g, d, eps, threadIdx.x & 63, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nullptr,
+                y + (size_t)row * d);
 }
 
 hipError_t launch_rmsnorm(const uint16_t* x, const uint16_t* gamma, int n_host, const int32_t* n_dev, int cap, int d,
@@ -83,7 +82,35 @@ hipError_t launch_rmsnorm(const uint16_t* x, const uint16_t* gamma, int n_host, 
     if (rows <= 0) return hipSuccess;
     if (d % 8 || d / 8 > 64 * RMS_MAXG) return hipErrorInvalidValue;
     RowCount rc{n_dev, n_host, cap};
-    hipLaunchKernelGGL(rmsnorm_kernel, dim3((rows + 3) / 4), dim3(256), 0, s, x, gamma, rc, d, eps, y);
+    hipLaunchKernelGGL(rmsnorm_kernel, dim3(rows), dim3(64 * RMS_NW), 0, s, x, gamma, rc, d, eps, y);
+    return hipGetLastError();
+}
+
+// The start of a canonical forward, one block per item: its entry of the item table (tab[i][0] =
+// its position p, tab[i][1 + k] = its row's page of slot min(k, p / 16)), x[i] = embed[token of
+// item i] and h[i] = RMSNorm(x[i]) (three launches of 4 to 6 us before).
+__global__ __launch_bounds__(64 * RMS_NW) void first_norm_kernel(Items it, const uint16_t* __restrict__ E,
+                                                         const uint16_t* __restrict__ g, int d, float eps, int mpr,
+                                                         int32_t* __restrict__ tab, uint16_t* __restrict__ x,
+                                                         uint16_t* __restrict__ h) {
+    const int i = blockIdx.x;
+    if (i >= items_n(it)) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = items_row(it, i), p = items_pos(it, i);
+    const int32_t* ptab = it.page_table + (size_t)r * mpr;
+    int32_t* tb = tab + (size_t)i * (1 + mpr);
+    if (threadIdx.x == 0) tb[0] = p;
+    for (int k = threadIdx.x; k < mpr; k += 64 * RMS_NW) tb[1 + k] = ptab[min(k, p >> 4)];
+    rmsnorm_row(E + (size_t)items_tok(it, i) * d, g, d, eps, threadIdx.x & 63, wave, x + (size_t)i * d,
+                   h + (size_t)i * d);
+}
+
+hipError_t launch_first_norm(const Items& it, const ModelDims& m, const uint16_t* embed, const uint16_t* gamma,
+                             int32_t* itab, uint16_t* x, uint16_t* h, hipStream_t s) {
+    if (it.n_host <= 0) return hipSuccess;
+    if (m.d % 8 || m.d / 8 > 64 * RMS_MAXG) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(first_norm_kernel, dim3(it.n_host), dim3(64 * RMS_NW), 0, s, it, embed, gamma, m.d, m.eps,
+                       m.max_pages_per_row, itab, x, h);
     return hipGetLastError();
 }
 

@@ -251,10 +251,9 @@ mg_status canon_forward(mg_ctx* c, const Items& it, uint16_t* own_col, float* lo
     uint16_t* att = c->at<uint16_t>(c->plan.att);
     uint16_t* act = c->at<uint16_t>(c->plan.act);
     int32_t* itab = c->at<int32_t>(c->plan.itab);
-    HIPCHK(launch_item_table(it, m, itab, s));
-    HIPCHK(launch_embed(it, c->W(0), d, x, s));
+    HIPCHK(launch_first_norm(it, m, c->W(0), c->LW(0, 0), itab, x, h, s));
     for (int l = 0; l < g.n_layers; ++l) {
-        HIPCHK(launch_rmsnorm(x, c->LW(l, 0), n, nd, cap, d, g.rms_eps, h, s));
+        if (l) HIPCHK(launch_rmsnorm(x, c->LW(l, 0), n, nd, cap, d, g.rms_eps, h, s));
         {
             const uint16_t* W[3] = {c->LW(l, 1), c->LW(l, 2), c->LW(l, 3)};
             const uint16_t* B[3] = {c->LW(l, 4), c->LW(l, 5), c->LW(l, 6)};

@@ -120,7 +120,9 @@ hipError_t launch_resid_norm(int B, const float* part, int S, const uint16_t* em
 // act[r] = bf16(silu(bf16(sum gate partials)) * bf16(sum up partials)); part rows [gate F | up F]
 hipError_t launch_swiglu_part(int B, const float* part, int S, int F, uint16_t* act, hipStream_t s);
 // ---------------------------------------------------------------- small kernels
-hipError_t launch_embed(const Items& it, const uint16_t* embed, int d, uint16_t* x, hipStream_t s);
+// item table, x = embedding rows and h = RMSNorm(x) of a canonical forward's items
+hipError_t launch_first_norm(const Items& it, const ModelDims& m, const uint16_t* embed, const uint16_t* gamma,
+                             int32_t* itab, uint16_t* x, uint16_t* h, hipStream_t s);
 hipError_t launch_rmsnorm(const uint16_t* x, const uint16_t* gamma, int n_host, const int32_t* n_dev, int cap, int d,
                           float eps, uint16_t* y, hipStream_t s);
 // RoPE of q and k for each item, q' -> qrot; K', V -> destination:
@@ -147,12 +149,11 @@ struct AttnArgs {
     uint16_t* out;             // [n][Hq*hd]
     // item table (or NULL): per item, its position then the page of every page slot of its row
     // clamped to the position's page, [n][1 + max_pages_per_row]; written once per forward by
-    // launch_item_table, so a block finds its position and pages in one memory round trip
+    // launch_first_norm, so a block finds its position and pages in one memory round trip
     const int32_t* itab;
     int n_cu;                  // compute units of the device (chooses the block size)
 };
 hipError_t launch_attention(const AttnArgs& a, int canon, hipStream_t s);  // canonical (canon = 1) only
-hipError_t launch_item_table(const Items& it, const ModelDims& m, int32_t* itab, hipStream_t s);
 
 // fast path: QKV split sum + bias + RoPE + tentative K/V append + attention, one block
 // per (row, KV head); rows 0..B-1 of the step batch
