@@ -124,7 +124,7 @@ mg_status mg_margin_gate(mg_ctx* ctx, int B, const float* logits, const uint8_t*
  * a context: code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same outputs and the same bits as mg_margin_gate over B rows of V logits
  * (B <= 256, V >= 2, else MG_ERR_ARG), without the host-mirror count.  Its partial states
- * live in a static device array of 32 KiB per GPU, held until the process ends; the first
+ * live in a static device array of 33 KiB per GPU, held until the process ends; the first
  * call on a device looks up that array's address (no allocation, no context).  Every call
  * on one GPU shares that array: calls that overlap on one GPU (different streams, or
  * different host threads) race and must be serialised by the caller.  All pointers

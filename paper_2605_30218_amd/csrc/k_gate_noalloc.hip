@@ -1,6 +1,6 @@
 // k_gate_noalloc.hip -- mg_margin_gate_noalloc: the margin gate for callers that cannot
 // allocate device memory (code under HIP graph capture, tight serving loops, harnesses that
-// forbid hipMalloc).  It runs the same two top-2 kernels as mg_margin_gate, with their
+// forbid hipMalloc).  It runs the same top-2 kernels as mg_margin_gate, with their
 // per-slice partial states kept in a file-scope device array instead of a context's
 // workspace, so it needs no context and no allocation.
 #include <mutex>
@@ -17,7 +17,8 @@ constexpr int MAX_DEVICES = 64;
 
 // One copy per GPU the library runs on, held until the process ends.  In host code this
 // name is only a stand-in for the device symbol: kernels get the address looked up below.
-static __device__ __align__(256) unsigned char scratch[GATE_SCRATCH_BYTES];
+// The arrival counters of single-launch gates follow the states (zero when the library is loaded).
+static __device__ __align__(256) unsigned char scratch[GATE_SCRATCH_BYTES + mg::TOP2_COUNTERS * sizeof(unsigned)];
 
 std::mutex g_mu;
 void* g_scratch_ptr[MAX_DEVICES];
@@ -52,10 +53,11 @@ extern "C" mg_status mg_margin_gate_noalloc(int B, int V, const float* logits, c
     if (mg::top2_ws_bytes(B, V) > GATE_SCRATCH_BYTES) return MG_ERR_WORKSPACE;
     void* ws = nullptr;
     if (scratch_on_current_device(&ws) != hipSuccess) return MG_ERR_HIP;
-    // every partial state the second kernel reads is written by the first one in the same
-    // call, so the array needs no clearing between calls
+    // every partial state that is read is written in the same call, and the counters are left at zero,
+    // so the array needs no clearing between calls
     if (mg::launch_top2(B, V, logits, protected_mask, tau, top1, margin, gate, gated_rows, n_gated, nullptr, ws,
-                        nullptr, static_cast<hipStream_t>(stream)) != hipSuccess)
+                        reinterpret_cast<unsigned*>(static_cast<unsigned char*>(ws) + GATE_SCRATCH_BYTES), nullptr,
+                        static_cast<hipStream_t>(stream)) != hipSuccess)
         return MG_ERR_HIP;
     return MG_OK;
 }

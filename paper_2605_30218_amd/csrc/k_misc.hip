@@ -211,15 +211,8 @@ hipError_t launch_rope_kv(const Items& it, const ModelDims& m, int layer, const 
 // ------------------------------------------------------------------ top-1 / top-2
 constexpr int TOP2_MAX_SLICES = 128;
 
-// Stage 1: block (s, b) scans slice s of row b (16-byte loads), merges its lanes by
-// wave shuffles and its waves through LDS, and stores the slice's state.
-__global__ __launch_bounds__(256) void top2_slice_kernel(int B, int V, int slice, const float* __restrict__ logits,
-                                                         Top2* __restrict__ part, int nsl, const int32_t* n_dev) {
-    const int s = blockIdx.x, b = blockIdx.y;
-    const int nrows = n_dev ? min(max(*n_dev, 0), B) : B;
-    if (b >= nrows) return;
-    const float* row = logits + (size_t)b * V;
-    const int j0 = s * slice, j1 = min(j0 + slice, V);
+// This thread's part of values j0 .. j1 - 1 of a row, merged over its wave (256 threads; 16-byte loads)
+__device__ __forceinline__ Top2 top2_scan(const float* row, int V, int j0, int j1) {
     Top2 st{-__builtin_inff(), -__builtin_inff(), -1, 0};
     const int t = threadIdx.x;
     if ((V & 3) == 0) {  // slice is a multiple of 4, so are j0 and j1
@@ -236,6 +229,57 @@ __global__ __launch_bounds__(256) void top2_slice_kernel(int B, int V, int slice
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) st = top2_merge(st, top2_shfl(st, o));
+    return st;
+}
+
+// row b's outputs from its merged state; whether its gate fires
+__device__ __forceinline__ uint8_t top2_gate_row(const Top2& st, int b, const uint8_t* prot, float tau, int32_t* top1,
+                                                 float* margin, uint8_t* gate) {
+    const int i1 = st.i1 < 0 ? 0 : st.i1;
+    const float g = st.nan ? __builtin_nanf("") : st.v1 - st.v2;
+    int fire = 0;
+    top1[b] = i1;
+    if (margin) margin[b] = g;
+    if (gate) {
+        const int p = prot ? (prot[b] != 0) : 1;
+        fire = p && !(g >= tau);
+        gate[b] = (uint8_t)fire;
+    }
+    return (uint8_t)fire;
+}
+
+// the firing rows in increasing order and their count (thread t of a block of at least 256; rows
+// 0..255 -> waves 0..3 of 64 rows: ballot, then prefix over the waves; one barrier)
+__device__ __forceinline__ void top2_compact(int t, int nrows, const uint8_t* fire_s, int* wave_cnt, int32_t* gated_rows,
+                                             int32_t* n_gated, int32_t* n_gated_host) {
+    const int w = t >> 6, l = t & 63;
+    const int f = (t < nrows) ? fire_s[t] : 0;  // t < 256 whenever t < nrows
+    const unsigned long long bal = __ballot(f);
+    if (w < 4 && l == 0) wave_cnt[w] = __popcll(bal);
+    __syncthreads();
+    if (w < 4) {
+        int base = 0;
+        for (int k = 0; k < w; ++k) base += wave_cnt[k];
+        if (f) gated_rows[base + __popcll(bal & ((1ull << l) - 1ull))] = t;
+        if (t == 0) {
+            const int cnt = wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
+            *n_gated = cnt;
+            // mirror for a host that polls pinned memory (a system-scope release store; the
+            // device-side consumers of the rows are ordered by the stream)
+            if (n_gated_host) __hip_atomic_store(n_gated_host, cnt, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+}
+
+// Stage 1: block (s, b) scans slice s of row b, merges its waves through LDS, and stores the
+// slice's state.
+__global__ __launch_bounds__(256) void top2_slice_kernel(int B, int V, int slice, const float* __restrict__ logits,
+                                                         Top2* __restrict__ part, int nsl, const int32_t* n_dev) {
+    const int s = blockIdx.x, b = blockIdx.y;
+    const int nrows = n_dev ? min(max(*n_dev, 0), B) : B;
+    if (b >= nrows) return;
+    const int t = threadIdx.x;
+    const Top2 st = top2_scan(logits + (size_t)b * V, V, s * slice, min((s + 1) * slice, V));
     __shared__ Top2 ws[4];
     if ((t & 63) == 0) ws[t >> 6] = st;
     __syncthreads();
@@ -261,41 +305,55 @@ __global__ __launch_bounds__(1024) void top2_final_kernel(int B, const Top2* __r
     for (int o = 1; o < tpr; o <<= 1) st = top2_merge(st, top2_shfl(st, o));
     __shared__ uint8_t fire_s[256];
     __shared__ int wave_cnt[4];
-    if (t % tpr == 0 && b < B) {
-        int fire = 0;
-        if (live) {
-            const int i1 = st.i1 < 0 ? 0 : st.i1;
-            const float g = st.nan ? __builtin_nanf("") : st.v1 - st.v2;
-            top1[b] = i1;
-            if (margin) margin[b] = g;
-            if (gate) {
-                const int p = prot ? (prot[b] != 0) : 1;
-                fire = p && !(g >= tau);
-                gate[b] = (uint8_t)fire;
-            }
-        }
-        fire_s[b] = (uint8_t)fire;
-    }
+    if (t % tpr == 0 && b < B) fire_s[b] = live ? top2_gate_row(st, b, prot, tau, top1, margin, gate) : 0;
     if (!gated_rows) return;
     __syncthreads();  // fire_s complete
-    // rows 0..255 -> waves 0..3 of 64 rows: ballot, then prefix over the waves
-    const int w = t >> 6, l = t & 63;
-    const int f = (t < nrows) ? fire_s[t] : 0;  // t < 256 whenever t < nrows
-    const unsigned long long bal = __ballot(f);
-    if (w < 4 && l == 0) wave_cnt[w] = __popcll(bal);
-    __syncthreads();
-    if (w < 4) {
-        int base = 0;
-        for (int k = 0; k < w; ++k) base += wave_cnt[k];
-        if (f) gated_rows[base + __popcll(bal & ((1ull << l) - 1ull))] = t;
-        if (t == 0) {
-            const int cnt = wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
-            *n_gated = cnt;
-            // mirror for a host that polls pinned memory (a system-scope release store; the
-            // device-side consumers of the rows are ordered by the stream)
-            if (n_gated_host) __hip_atomic_store(n_gated_host, cnt, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
+    top2_compact(t, nrows, fire_s, wave_cnt, gated_rows, n_gated, n_gated_host);
+}
+
+// Both stages in one launch for up to 256 slice states (few rows, or a small vocabulary): the block
+// that finishes last merges them.  The second launch it saves costs more than the arrival counter:
+// one row of 128256 values takes 8.1 us a call instead of 10.7 (the host's launches; 7.6 and 7.2 us of
+// kernels), 5 rows of 4096 5.5 us instead of 4.8 + 4.7.  The states are stored before the counter is incremented
+// (release) and read after (acquire).  atomicInc wraps to 0 at the launch's own block count and every
+// block count has a counter of its own, so a launch leaves its counter as it found it.
+__global__ __launch_bounds__(256) void top2_single_kernel(int B, int V, int slice, const float* __restrict__ logits,
+                                                          Top2* part, int nsl, unsigned* counters,
+                                                          const uint8_t* __restrict__ prot, float tau, int32_t* top1,
+                                                          float* margin, uint8_t* gate, int32_t* gated_rows,
+                                                          int32_t* n_gated, int32_t* n_gated_host,
+                                                          const int32_t* n_dev) {
+    const int s = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
+    const int nrows = n_dev ? min(max(*n_dev, 0), B) : B;
+    __shared__ Top2 ws[4];
+    __shared__ int last;
+    if (b < nrows) {
+        const Top2 st = top2_scan(logits + (size_t)b * V, V, s * slice, min((s + 1) * slice, V));
+        if ((t & 63) == 0) ws[t >> 6] = st;
     }
+    __syncthreads();
+    if (t == 0) {
+        if (b < nrows) part[b * nsl + s] = top2_merge(top2_merge(ws[0], ws[1]), top2_merge(ws[2], ws[3]));
+        const unsigned total = gridDim.x * gridDim.y;
+        __threadfence();
+        last = atomicInc(counters + total, total - 1) == total - 1;
+        __threadfence();
+    }
+    __syncthreads();
+    if (!last) return;
+    // state t of row t / nsl (nsl a power of two up to 64, B * nsl <= 256)
+    const int row = t / nsl;
+    Top2 st{-__builtin_inff(), -__builtin_inff(), -1, 0};
+    if (row < nrows) st = part[t];
+    for (int o = 1; o < nsl; o <<= 1) st = top2_merge(st, top2_shfl(st, o));
+    __shared__ uint8_t fire_s[256];
+    __shared__ int wave_cnt[4];
+    fire_s[t] = 0;
+    __syncthreads();
+    if (t % nsl == 0 && row < nrows) fire_s[row] = top2_gate_row(st, row, prot, tau, top1, margin, gate);
+    if (!gated_rows) return;
+    __syncthreads();
+    top2_compact(t, nrows, fire_s, wave_cnt, gated_rows, n_gated, n_gated_host);
 }
 
 int top2_slices(int B, int V) {
@@ -305,19 +363,35 @@ int top2_slices(int B, int V) {
     return nsl;
 }
 
+// slices of a single-launch gate, or 0: at most 64 (one row's states in one wave) and 256 states,
+// and no slice more than 4 times as long as the two-launch form's
+static int top2_single_slices(int B, int V) {
+    const int two = top2_slices(B, V);
+    int nsl = two < 64 ? two : 64;
+    while (nsl > 1 && nsl * B > 256) nsl /= 2;
+    return nsl * B <= 256 && nsl * 4 >= two ? nsl : 0;
+}
+
 size_t top2_ws_bytes(int B, int V) {
     return B <= 0 ? 0 : (size_t)top2_slices(B, V) * B * sizeof(Top2);
 }
 
 hipError_t launch_top2(int B, int V, const float* logits, const uint8_t* prot, float tau, int32_t* top1, float* margin,
                        uint8_t* gate, int32_t* gated_rows, int32_t* n_gated, int32_t* n_gated_host, void* part_ws,
-                       const int32_t* n_dev, hipStream_t s) {
+                       unsigned* counters, const int32_t* n_dev, hipStream_t s) {
     if (B <= 0) return hipSuccess;
     if (B > 256) return hipErrorInvalidValue;
+    Top2* part = static_cast<Top2*>(part_ws);
+    const int one = top2_single_slices(B, V);
+    if (one) {
+        const int slice = ((V + one - 1) / one + 3) & ~3;
+        hipLaunchKernelGGL(top2_single_kernel, dim3(one, B), dim3(256), 0, s, B, V, slice, logits, part, one, counters,
+                           prot, tau, top1, margin, gate, gated_rows, n_gated, n_gated_host, n_dev);
+        return hipGetLastError();
+    }
     const int nsl = top2_slices(B, V);
     int slice = (V + nsl - 1) / nsl;
     slice = (slice + 3) & ~3;
-    Top2* part = static_cast<Top2*>(part_ws);
     hipLaunchKernelGGL(top2_slice_kernel, dim3(nsl, B), dim3(256), 0, s, B, V, slice, logits, part, nsl, n_dev);
     hipLaunchKernelGGL(top2_final_kernel, dim3(1), dim3(1024), 0, s, B, part, nsl, prot, tau, top1, margin, gate,
                        gated_rows, n_gated, n_gated_host, n_dev);

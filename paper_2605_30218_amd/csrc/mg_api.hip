@@ -26,7 +26,7 @@ constexpr size_t ALIGN = 256;
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Plan {
-    size_t rope, x, h, qkv, qrot, att, act, attn_part, itab, gemm_part, top2_ws, vlog, vrows, total;
+    size_t rope, x, h, qkv, qrot, att, act, attn_part, itab, gemm_part, top2_ws, top2_cnt, vlog, vrows, total;
     int rows_cap, max_pos, chunks_canon;
 };
 
@@ -92,6 +92,7 @@ Plan make_plan(const mg_model_cfg* c, int n_cu) {
         }
     p.gemm_part = o; o += up((gp ? gp : 1) * sizeof(float));
     p.top2_ws = o; o += up(TOP2_WS_BYTES);
+    p.top2_cnt = o; o += up(TOP2_COUNTERS * sizeof(unsigned));
     p.vlog = o; o += up((size_t)c->max_batch * c->vocab * sizeof(float));
     // the matrix-core verifier's compact rows: token, position, page-table row, and the
     // top-2 pass's margin / gate / row list / count
@@ -386,6 +387,7 @@ mg_status mg_create(const mg_model_cfg* cfg, const void* const* weights, void* k
         }
     }
     if (hipMemcpy(c->at<float>(plan.rope), cs.data(), cs.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemset(c->at<unsigned>(plan.top2_cnt), 0, TOP2_COUNTERS * sizeof(unsigned)) != hipSuccess ||
         hipDeviceSynchronize() != hipSuccess) {
         delete c;
         return MG_ERR_HIP;
@@ -535,7 +537,7 @@ mg_status mg_verify_rows_mfma(mg_ctx* c, int n, const int32_t* rows, const int32
     MGCHK(fast_forward(c, n, vtok, vpos, vpt, logits, v_kvcol, MFMA_VERIFIER_SPLIT_M, s));
     // v_tok = top-1 of each row (lowest index on ties); the gate outputs are scratch
     HIPCHK(launch_top2(n, c->cfg.vocab, logits, nullptr, 0.0f, v_tok, vmargin, vgate, vrowlist, vn, nullptr,
-                       c->at<void>(c->plan.top2_ws), nullptr, s));
+                       c->at<void>(c->plan.top2_ws), c->at<unsigned>(c->plan.top2_cnt), nullptr, s));
     return MG_OK;
 }
 
@@ -548,7 +550,7 @@ mg_status mg_margin_gate(mg_ctx* c, int B, const float* logits, const uint8_t* p
     hipStream_t s = static_cast<hipStream_t>(stream);
     ProfScope ps(c, MG_KIND_GATE, s, (double)B * c->cfg.vocab * 4.0);
     HIPCHK(launch_top2(B, c->cfg.vocab, logits, protected_mask, tau, top1, margin, gate, gated_rows, n_gated,
-                       n_gated_host, c->ws + c->plan.top2_ws, nullptr, s));
+                       n_gated_host, c->ws + c->plan.top2_ws, c->at<unsigned>(c->plan.top2_cnt), nullptr, s));
     return MG_OK;
 }
 
@@ -565,7 +567,7 @@ mg_status mg_verify_rows(mg_ctx* c, int n, const int32_t* rows, const int32_t* n
     float* lg = v_logits ? v_logits : c->at<float>(c->plan.vlog);
     MGCHK(canon_forward(c, it, v_kvcol, lg, s));
     HIPCHK(launch_top2(cap, c->cfg.vocab, lg, nullptr, 0.0f, v_tok, nullptr, nullptr, nullptr, nullptr, nullptr,
-                       c->ws + c->plan.top2_ws, it.n_dev, s));
+                       c->ws + c->plan.top2_ws, c->at<unsigned>(c->plan.top2_cnt), it.n_dev, s));
     return MG_OK;
 }
 

@@ -1,0 +1,82 @@
+"""The margin gate where its slices are few enough for one launch, and on both sides of that limit:
+against the oracle, called again and again with other shapes in between (a launch leaves its
+arrival counter at zero), and replayed from a graph between eager calls."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import mgo
+from paper_2605_30218_amd import mg
+
+pytestmark = pytest.mark.gpu
+
+# one row (64 slices), odd and tiny vocabularies, 256 slice states exactly, one slice a row, and
+# (5, 128256), (17, 32064), (200, 8192) past the limit
+SHAPES = [(1, 128256), (1, 2), (2, 5), (3, 1023), (4, 128257), (5, 128256), (16, 32064), (17, 32064), (64, 4096),
+          (65, 4096), (128, 3000), (200, 8192), (256, 40)]
+
+
+def logits(B, V, seed):
+    rng = np.random.RandomState(seed)
+    L = rng.standard_normal((B, V)).astype(np.float32)
+    L[0, V - 1] = L[0].max()                       # ties: the lowest index wins
+    if B > 1:
+        L[1] = 0.25                                # all equal
+    if B > 2:
+        L[2, V // 2] = np.nan
+    if B > 3:
+        L[3] = -np.inf
+    if B > 4:
+        L[4] = np.finfo(np.float32).min
+        L[4, V // 3] = np.inf
+    return L
+
+
+def outputs(B):
+    return [torch.full((B,), -7, dtype=torch.int32, device="cuda"), torch.full((B,), -7.0, device="cuda"),
+            torch.full((B,), 9, dtype=torch.uint8, device="cuda"), torch.full((B,), -7, dtype=torch.int32, device="cuda"),
+            torch.full((1,), -7, dtype=torch.int32, device="cuda")]
+
+
+def check(out, L, prot, tau):
+    t, m, g, r = mgo.OracleModel.margin_gate(L, prot, tau)
+    n = int(out[4].cpu())
+    np.testing.assert_array_equal(out[0].cpu().numpy(), t)
+    gm = out[1].cpu().numpy()
+    np.testing.assert_array_equal(np.isnan(gm), np.isnan(m))
+    np.testing.assert_array_equal(gm[~np.isnan(m)].view(np.uint32), m[~np.isnan(m)].view(np.uint32))
+    np.testing.assert_array_equal(out[2].cpu().numpy(), g)
+    np.testing.assert_array_equal(out[3].cpu().numpy()[:n], r)
+    assert n == len(r)
+
+
+def test_against_the_oracle_in_turn():
+    for rnd in range(3):
+        for B, V in SHAPES:
+            L = logits(B, V, 10 * rnd + B)
+            prot = (np.arange(B) % 5 != 3).astype(np.uint8)
+            out = outputs(B)
+            mg.margin_gate_noalloc(B, V, torch.as_tensor(L).cuda(), torch.as_tensor(prot).cuda(), 0.3, *out)
+            torch.cuda.synchronize()
+            check(out, L, prot, 0.3)
+
+
+@pytest.mark.parametrize("B,V", [(1, 128256), (5, 4096)])
+def test_graph_replays(B, V):
+    L = [logits(B, V, s) for s in range(4)]
+    buf = torch.as_tensor(L[0]).cuda()
+    out = outputs(B)
+    mg.margin_gate_noalloc(B, V, buf, None, 0.3, *out)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        mg.margin_gate_noalloc(B, V, buf, None, 0.3, *out)
+    for k in range(4):
+        buf.copy_(torch.as_tensor(L[k]))
+        g.replay()
+        torch.cuda.synchronize()
+        check(out, L[k], None, 0.3)
+        other = outputs(B)
+        mg.margin_gate_noalloc(B, V, torch.as_tensor(L[k - 1]).cuda(), None, 0.3, *other)  # eager, in between
+        torch.cuda.synchronize()
+        check(other, L[k - 1], None, 0.3)
