@@ -82,8 +82,8 @@ mg_status mg_op_fast_gemm_config(int n, int N, int K, int n_cu, int* S, int* wav
 mg_status mg_op_canon_gemv_config(int n, int N, int K, int swiglu, int n_cu, int* kernel, int* tile_rows, int* quads,
                                   int* waves, int* depth);
 
-/* y[r] = RMSNorm(x[r]) * gamma with the canonical sum of squares (one wave per
- * row, CDOT order), r < n; d % 8 == 0.  bf16 in, bf16 out. */
+/* y[r] = RMSNorm(x[r]) * gamma with the canonical sum of squares (CDOT order), r < n;
+ * d % 8 == 0; y may be x.  bf16 in, bf16 out. */
 mg_status mg_op_rmsnorm(int n, int d, const uint16_t* x, const uint16_t* gamma, float eps, uint16_t* y, void* stream);
 
 /* mg_decode_step (the BF16 fast path of Sec. 3.1, with its tentative K/V append of

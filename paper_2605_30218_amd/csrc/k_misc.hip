@@ -11,8 +11,9 @@ namespace mg {
 // m = ss / d, r = 1 / sqrt(m + eps), y_i = bf16((x_i * r) * gamma_i).
 // The order of the sum leaves one wave per row for it, and a lone wave is bound by its own
 // instruction stream (a vector instruction every 4 cycles: 8 per value for the output alone).  So
-// four waves take a row: each forms the whole sum for itself (no exchange, no barrier) and writes
-// every fourth 64-group slice of the output.  Against one wave per row: 4.9 and 6.6 us at 5 rows of
+// four waves take a row: each forms the whole sum for itself (no exchange) and writes
+// every fourth 64-group slice of the output, past a barrier, so that y may be x (a wave alone read
+// the whole row before it wrote).  Against one wave per row: 4.9 and 6.6 us at 5 rows of
 // 4096 values, 4.9 and 7.6 at 18 of 5120, 5.0 and 7.1 at 64 and 6.5 and 8.0 at 1000 of 4096.
 constexpr int RMS_MAXG = 16;  // groups of 8 per lane: d <= 8192
 constexpr int RMS_NW = 4;     // waves per row
@@ -51,6 +52,7 @@ __device__ __forceinline__ void rmsnorm_row(const uint16_t* src, const uint16_t*
     const float ss = butterfly_sum(a);
     const float m = ieee_div(ss, (float)d);
     const float r = ieee_div(1.0f, ieee_sqrt(m + eps));
+    __syncthreads();  // every wave's loads of the row are before every store
     uint4* yr = reinterpret_cast<uint4*>(y);
 #pragma unroll
     for (int k = 0; k < NO; ++k) {
@@ -68,8 +70,8 @@ __device__ __forceinline__ void rmsnorm_row(const uint16_t* src, const uint16_t*
     }
 }
 
-__global__ __launch_bounds__(64 * RMS_NW) void rmsnorm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ g,
-                                                              RowCount rc, int d, float eps, uint16_t* __restrict__ y) {
+__global__ __launch_bounds__(64 * RMS_NW) void rmsnorm_kernel(const uint16_t* x, const uint16_t* __restrict__ g,
+                                                              RowCount rc, int d, float eps, uint16_t* y) {
     const int row = blockIdx.x;
     if (row >= rc.get()) return;
     rmsnorm_row(x + (size_t)row * d, g, d, eps, threadIdx.x & 63, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nullptr,
