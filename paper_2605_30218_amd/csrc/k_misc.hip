@@ -313,11 +313,28 @@ __global__ __launch_bounds__(1024) void top2_final_kernel(int B, const Top2* __r
     top2_compact(t, nrows, fire_s, wave_cnt, gated_rows, n_gated, n_gated_host);
 }
 
+// A slice state for another block of the same launch: agent-scope words, which go past the L2s of
+// the XCDs by themselves
+__device__ __forceinline__ void top2_store_agent(Top2* p, const Top2& st) {
+    const unsigned w[4] = {__float_as_uint(st.v1), __float_as_uint(st.v2), (unsigned)st.i1, (unsigned)st.nan};
+    unsigned* d = reinterpret_cast<unsigned*>(p);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) __hip_atomic_store(d + k, w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ Top2 top2_load_agent(Top2* p) {
+    unsigned w[4];
+    unsigned* d = reinterpret_cast<unsigned*>(p);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = __hip_atomic_load(d + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return Top2{__uint_as_float(w[0]), __uint_as_float(w[1]), (int)w[2], (int)w[3]};
+}
+
 // Both stages in one launch for up to 256 slice states (few rows, or a small vocabulary): the block
 // that finishes last merges them.  The second launch it saves costs more than the arrival counter:
-// one row of 128256 values takes 8.1 us a call instead of 10.7 (the host's launches; 7.6 and 7.2 us of
-// kernels), 5 rows of 4096 5.5 us instead of 4.8 + 4.7.  The states are stored before the counter is incremented
-// (release) and read after (acquire).  atomicInc wraps to 0 at the launch's own block count and every
+// one row of 128256 values takes 7.0 us a call instead of 9.4, 5 rows of 4096 7.0 instead of 10, 64 rows
+// of 4096 (256 blocks) 8.1 instead of 10.1.  A state is stored past the L2 and waited for before the
+// counter is incremented, and read after; a release fence instead writes back an XCD's L2 in every block
+// (64 rows of 4096: 11.7 us of kernel time).  atomicInc wraps to 0 at the launch's own block count and every
 // block count has a counter of its own, so a launch leaves its counter as it found it.
 __global__ __launch_bounds__(256) void top2_single_kernel(int B, int V, int slice, const float* __restrict__ logits,
                                                           Top2* part, int nsl, unsigned* counters,
@@ -335,18 +352,19 @@ __global__ __launch_bounds__(256) void top2_single_kernel(int B, int V, int slic
     }
     __syncthreads();
     if (t == 0) {
-        if (b < nrows) part[b * nsl + s] = top2_merge(top2_merge(ws[0], ws[1]), top2_merge(ws[2], ws[3]));
+        if (b < nrows) top2_store_agent(&part[b * nsl + s], top2_merge(top2_merge(ws[0], ws[1]), top2_merge(ws[2], ws[3])));
         const unsigned total = gridDim.x * gridDim.y;
-        __threadfence();
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the state is stored
         last = atomicInc(counters + total, total - 1) == total - 1;
-        __threadfence();
+        asm volatile("" ::: "memory");
     }
     __syncthreads();
     if (!last) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the states' loads stay behind the counter
     // state t of row t / nsl (nsl a power of two up to 64, B * nsl <= 256)
     const int row = t / nsl;
     Top2 st{-__builtin_inff(), -__builtin_inff(), -1, 0};
-    if (row < nrows) st = part[t];
+    if (row < nrows) st = top2_load_agent(&part[t]);
     for (int o = 1; o < nsl; o <<= 1) st = top2_merge(st, top2_shfl(st, o));
     __shared__ uint8_t fire_s[256];
     __shared__ int wave_cnt[4];
@@ -365,13 +383,14 @@ int top2_slices(int B, int V) {
     return nsl;
 }
 
-// slices of a single-launch gate, or 0: at most 64 (one row's states in one wave) and 256 states,
-// and no slice more than 4 times as long as the two-launch form's
+// slices of a single-launch gate, or 0: at most 64 (one row's states in one wave) and 256 states, no
+// slice more than 4 times as long as the two-launch form's (18 rows of 32000 in 8 instead of 32: 8.2 us
+// against 10.1) or above 4096 values (8 rows of 152064 in slices of 4752: 10.3 against 10.1)
 static int top2_single_slices(int B, int V) {
     const int two = top2_slices(B, V);
     int nsl = two < 64 ? two : 64;
     while (nsl > 1 && nsl * B > 256) nsl /= 2;
-    return nsl * B <= 256 && nsl * 4 >= two ? nsl : 0;
+    return nsl * B <= 256 && nsl * 4 >= two && V <= 4096L * nsl ? nsl : 0;
 }
 
 size_t top2_ws_bytes(int B, int V) {
