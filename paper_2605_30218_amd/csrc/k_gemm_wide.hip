@@ -269,13 +269,20 @@ struct WideLaunch {
 // from HBM at 2375 bytes a cycle over the chip, at most 13 a CU.  LDS reads and MFMAs of a chunk
 // take about 1.5 times the LDS port's time (4 WN (MT + NT) KiB read and 64 (BM + BN) bytes written
 // per k-step of 32, 128 bytes a cycle).  4 us to start and end; split tiles are written and
-// read once at about 2 KB a cycle.  For the projections of the three models at 80, 128 and 251
-// rows its choice was within 4% of the fastest of all tiles and splits (measured one by one).
+// read once at about 2 KB a cycle.  The busiest CU is one of the XCD that gets the most blocks: the
+// feature blocks are dealt to the XCDs whole, so 26 of them in 9 splits are 36 blocks for the 32
+// CUs of two XCDs, a second round, though the chip has 256 CUs for 234 blocks (4096 x 14336 at 65
+// rows 43 us so, 26 in 8 splits of 32 blocks an XCD; 3584 x 18944 at 128 rows 50 in 36 blocks an XCD,
+// 35 in 27).  The tile that it takes for a split count is within 5% of the fastest one there for
+// the QKV, O and down projections of the three models at 65..251 rows (all tiles measured one by
+// one; 16% at 129 rows of 7168 x 5120); another split count would be up to a fifth faster where
+// three or four splits of a down projection leave CUs idle (251 rows of 4096 x 14336: 58 us, 48 in 4).
 static double wide_cost(int M, int N, int K, int MT, int NT, int WN, int S, int n_cu) {
     const int BM = 64 * MT, BN = 16 * NT * WN, nrb = (M + BM - 1) / BM;
-    const long blocks = (long)((N + BN - 1) / BN) * nrb * S;
+    const long blocks = (long)(((N + BN - 1) / BN + 7) / 8) * nrb * S;  // of the XCD that has the most
+    const long xcd_cu = n_cu >= 8 ? n_cu / 8 : 1;
     const long units = K / 128, ksteps = (units + S - 1) / S * 4;
-    const double steps = (double)((blocks + n_cu - 1) / n_cu) * ksteps;  // k-steps of the busiest CU
+    const double steps = (double)((blocks + xcd_cu - 1) / xcd_cu) * ksteps;  // k-steps of the busiest CU
     const double l2 = steps * 2.0 * (BM + BN * (1.0 - 1.0 / nrb));
     const double hbm_chip = (double)N * K * 2 / 2375.0, hbm_cu = steps * BN * 64.0 / nrb / 13.0;
     const double mem = l2 + (hbm_chip > hbm_cu ? hbm_chip : hbm_cu);

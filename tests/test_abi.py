@@ -127,6 +127,15 @@ def test_fast_gemm_launch_rule():
         mg.fast_gemm_config(0, 64, 512)
 
 
+def test_wide_gemm_splits_count_the_blocks_of_one_xcd():
+    """Above 64 rows the feature blocks go to the 8 XCDs whole, so what a split count costs is set by
+    the XCD that gets the most blocks: 26 feature blocks in 9 splits are 36 blocks for 32 CUs (a
+    second round), and 23 in 11 splits 33, though the chip has CUs enough for all."""
+    assert mg.fast_gemm_config(65, 4096, 14336)[0] == 8
+    assert [mg.fast_gemm_config(n, 3584, 18944)[0] for n in (65, 72)] == [10, 10]
+    assert mg.fast_gemm_config(128, 4096, 14336)[0] == 7  # 28 blocks an XCD: one round
+
+
 def test_canon_gemv_launch_rule():
     """The verifier's canonical GEMV launch, host logic only: the vector-fma kernel up to 8
     rows, the matrix-core kernel above; one 16-row tile up to 16 rows and from 25 to 48, a
