@@ -57,7 +57,7 @@ extern "C" mg_status mg_margin_gate_noalloc(int B, int V, const float* logits, c
     // so the array needs no clearing between calls
     if (mg::launch_top2(B, V, logits, protected_mask, tau, top1, margin, gate, gated_rows, n_gated, nullptr, ws,
                         reinterpret_cast<unsigned*>(static_cast<unsigned char*>(ws) + GATE_SCRATCH_BYTES), nullptr,
-                        static_cast<hipStream_t>(stream)) != hipSuccess)
+                        true, static_cast<hipStream_t>(stream)) != hipSuccess)
         return MG_ERR_HIP;
     return MG_OK;
 }

@@ -537,7 +537,7 @@ mg_status mg_verify_rows_mfma(mg_ctx* c, int n, const int32_t* rows, const int32
     MGCHK(fast_forward(c, n, vtok, vpos, vpt, logits, v_kvcol, MFMA_VERIFIER_SPLIT_M, s));
     // v_tok = top-1 of each row (lowest index on ties); the gate outputs are scratch
     HIPCHK(launch_top2(n, c->cfg.vocab, logits, nullptr, 0.0f, v_tok, vmargin, vgate, vrowlist, vn, nullptr,
-                       c->at<void>(c->plan.top2_ws), c->at<unsigned>(c->plan.top2_cnt), nullptr, s));
+                       c->at<void>(c->plan.top2_ws), c->at<unsigned>(c->plan.top2_cnt), nullptr, false, s));
     return MG_OK;
 }
 
@@ -550,7 +550,7 @@ mg_status mg_margin_gate(mg_ctx* c, int B, const float* logits, const uint8_t* p
     hipStream_t s = static_cast<hipStream_t>(stream);
     ProfScope ps(c, MG_KIND_GATE, s, (double)B * c->cfg.vocab * 4.0);
     HIPCHK(launch_top2(B, c->cfg.vocab, logits, protected_mask, tau, top1, margin, gate, gated_rows, n_gated,
-                       n_gated_host, c->ws + c->plan.top2_ws, c->at<unsigned>(c->plan.top2_cnt), nullptr, s));
+                       n_gated_host, c->ws + c->plan.top2_ws, c->at<unsigned>(c->plan.top2_cnt), nullptr, true, s));
     return MG_OK;
 }
 
@@ -567,7 +567,7 @@ mg_status mg_verify_rows(mg_ctx* c, int n, const int32_t* rows, const int32_t* n
     float* lg = v_logits ? v_logits : c->at<float>(c->plan.vlog);
     MGCHK(canon_forward(c, it, v_kvcol, lg, s));
     HIPCHK(launch_top2(cap, c->cfg.vocab, lg, nullptr, 0.0f, v_tok, nullptr, nullptr, nullptr, nullptr, nullptr,
-                       c->ws + c->plan.top2_ws, c->at<unsigned>(c->plan.top2_cnt), it.n_dev, s));
+                       c->ws + c->plan.top2_ws, c->at<unsigned>(c->plan.top2_cnt), it.n_dev, false, s));
     return MG_OK;
 }
 

@@ -185,15 +185,16 @@ int fast_attn_splits(int rows, int n_kv_heads, int max_pages_per_row, int n_cu, 
 
 // ---------------------------------------------------------------- gate / repair / misc
 // top-1 / top-2 of B <= 256 logit rows in two launches (vocabulary slices, then a
-// per-row merge and the ordered compaction), or one where there are few slices; part_ws holds
-// TOP2_WS_BYTES, counters TOP2_COUNTERS words that were zero before the first launch
+// per-row merge and the ordered compaction), or one where there are few slices (alone: the call
+// is a gate by itself, whose launches on the host count); part_ws holds TOP2_WS_BYTES, counters
+// TOP2_COUNTERS words that were zero before the first launch
 constexpr size_t TOP2_WS_BYTES = 256 * 128 * 16;
 constexpr int TOP2_COUNTERS = 257;
 // bytes of part_ws a launch of B rows over V logits uses (at most 2048 slice states of 16 bytes)
 size_t top2_ws_bytes(int B, int V);
 hipError_t launch_top2(int B, int V, const float* logits, const uint8_t* prot, float tau, int32_t* top1,
                        float* margin, uint8_t* gate, int32_t* gated_rows, int32_t* n_gated, int32_t* n_gated_host,
-                       void* part_ws, unsigned* counters, const int32_t* n_dev, hipStream_t s);
+                       void* part_ws, unsigned* counters, const int32_t* n_dev, bool alone, hipStream_t s);
 // compact copies of the listed rows' token, position and page-table row
 hipError_t launch_gather_rows(int n, const int32_t* rows, const int32_t* tokens, const int32_t* positions,
                               const int32_t* page_table, int maxp, int32_t* out_tok, int32_t* out_pos, int32_t* out_pt,

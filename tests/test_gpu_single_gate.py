@@ -1,6 +1,8 @@
 """The margin gate where its slices are few enough for one launch, and on both sides of that limit:
 against the oracle, called again and again with other shapes in between (a launch leaves its
 arrival counter at zero), and replayed from a graph between eager calls."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -80,3 +82,32 @@ def test_graph_replays(B, V):
         mg.margin_gate_noalloc(B, V, torch.as_tensor(L[k - 1]).cuda(), None, 0.3, *other)  # eager, in between
         torch.cuda.synchronize()
         check(other, L[k - 1], None, 0.3)
+
+
+@pytest.mark.parametrize("B,V,launches", [(1, 128256, 1), (16, 4096, 1), (17, 4096, 2), (64, 4096, 2), (4, 32000, 1),
+                                          (16, 32000, 2), (8, 128256, 2), (1, 131071, 1), (1, 152063, 2)])
+def test_launches_in_a_graph(B, V, launches):
+    """In a graph no launch costs the host anything, and above 64 slice states the single launch
+    takes more of the GPU than the two: a captured gate is one launch up to there, two above (and
+    for slices above 2048 values of rows that are no 16-byte multiple)."""
+    L = [logits(B, V, s) for s in range(3)]
+    buf = torch.as_tensor(L[0]).cuda()
+    out = outputs(B)
+    hip = ctypes.CDLL("libamdhip64.so")
+    side = torch.cuda.Stream()
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t(0)
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(ctypes.c_void_p(side.cuda_stream), 2) == 0  # hipStreamCaptureModeRelaxed
+    mg.margin_gate_noalloc(B, V, buf, None, 0.3, *out, stream=side)
+    assert hip.hipStreamEndCapture(ctypes.c_void_p(side.cuda_stream), ctypes.byref(graph)) == 0
+    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    run = ctypes.c_void_p()
+    assert hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, ctypes.c_size_t(0)) == 0
+    assert n.value == launches
+    for k in range(3):
+        buf.copy_(torch.as_tensor(L[k]))
+        torch.cuda.synchronize()
+        assert hip.hipGraphLaunch(run, ctypes.c_void_p(side.cuda_stream)) == 0
+        torch.cuda.synchronize()
+        check(out, L[k], None, 0.3)
+    assert hip.hipGraphExecDestroy(run) == 0 and hip.hipGraphDestroy(graph) == 0
