@@ -626,10 +626,13 @@ static void launch_ft(const FastGemmArgs& a, int epi, dim3 g, hipStream_t s) {
 }
 
 // An unsplit output (the LM head) of 17 to 64 rows and so few features that 4-wave blocks leave
-// half of the CUs idle goes to the smaller tiles of k_gemm_wide.hip (4096 features at 64 rows: 17.8 us
-// in 256 blocks against 22.2 in 64; up to 16 rows the two are equal)
+// half of the CUs idle goes to the smaller tiles of k_gemm_wide.hip; up to 32 rows three quarters
+// of them idle.  Weights from HBM, 256..8192 features of 3584, 4096 and 5120 inputs: 33 to 64 rows take
+// 0.69 to 0.93 of the time (4096 x 4096 at 64 rows 17.2 us in 256 blocks, 21.8 in 64); 17 to 32 rows 0.83 to 0.99
+// up to 4096 features, but 1.04 to 0.94 above (6144 x 4096 at 17 rows 20.7 against 19.9 us); up to 16 rows the
+// two are equal
 static bool few_blocks(int epi, int M, int N, int K, int n_cu) {
-    return (epi == FEPI_F32 || epi == FEPI_TOP2) && M > 16 && lds_path(M, K) && (N + 63) / 64 <= n_cu / 2;
+    return (epi == FEPI_F32 || epi == FEPI_TOP2) && M > 16 && lds_path(M, K) && (N + 63) / 64 <= n_cu / (M > 32 ? 2 : 4);
 }
 
 template <int MT>

@@ -136,6 +136,16 @@ def test_wide_gemm_splits_count_the_blocks_of_one_xcd():
     assert mg.fast_gemm_config(128, 4096, 14336)[0] == 7  # 28 blocks an XCD: one round
 
 
+def test_unsplit_outputs_of_few_features():
+    """The LM head of 17 to 64 rows takes the small tiles of the wide kernel where 4-wave blocks of 64
+    features leave the chip idle: up to 8192 features (on 256 CUs) from 33 rows, up to 4096 below, where
+    they were measured slower above."""
+    blocks = mg.load()._ZN2mg16fast_gemm_blocksEiiii  # feature blocks of a launch (C++ linkage)
+    four_wave = lambda n, N: blocks(n, N, 4096, 256) in (N // 64, N // 128)
+    assert [four_wave(n, N) for n, N in [(17, 6144), (32, 6144), (32, 8192), (64, 8320), (16, 4096)]] == [True] * 5
+    assert [four_wave(n, N) for n, N in [(17, 4096), (32, 4096), (33, 6144), (64, 8192)]] == [False] * 4
+
+
 def test_canon_gemv_launch_rule():
     """The verifier's canonical GEMV launch, host logic only: the vector-fma kernel up to 8
     rows, the matrix-core kernel above; one 16-row tile up to 16 rows and from 25 to 48, a

@@ -30,9 +30,10 @@ def test_small_integers_exact(n, N, K):
 
 
 @pytest.mark.parametrize("n", [16, 17, 33, 64])
-@pytest.mark.parametrize("N", [16, 1040, 8192, 8208])
+@pytest.mark.parametrize("N", [16, 1040, 4096, 4112, 8192, 8208])
 def test_few_features_at_up_to_64_rows(n, N):
-    """Unsplit outputs on both sides of the 128 blocks of 64 features up to which 17 to 64 rows take it."""
+    """Unsplit outputs on both sides of the 64 blocks of 64 features up to which 17 to 32 rows take it,
+    and of the 128 for 33 to 64 rows."""
     X, W = synth.small_int_bf16((n, 512), seed=n), synth.small_int_bf16((N, 512), seed=N)
     Y = mg.op_linear(False, to_dev(X), to_dev(W)).cpu().numpy()
     ref = mgo.f32_from_bf16(X).astype(np.float64) @ mgo.f32_from_bf16(W).astype(np.float64).T
