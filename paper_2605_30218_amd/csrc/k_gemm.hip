@@ -651,7 +651,8 @@ hipError_t launch_fast_gemm(const FastGemmArgs& a, int epi, hipStream_t s) {
     if (epi != FEPI_PART && a.S != 1) return hipErrorInvalidValue;  // only partial tiles may be split
     if (epi == FEPI_SWIGLU && (a.S != 1 || !fast_gemm_lds_path(a.M, a.K) || a.Nseg[0] != a.N || a.Nseg[1] != a.N))
         return hipErrorInvalidValue;
-    if (wide_gemm_takes(a.M, a.K) || few_blocks(epi, a.M, a.N, a.K, a.n_cu > 0 ? a.n_cu : 256))
+    // (the wide kernel has no FEPI_BF16 epilogue: that one stays on the register operand path above 64 rows)
+    if (epi != FEPI_BF16 && (wide_gemm_takes(a.M, a.K) || few_blocks(epi, a.M, a.N, a.K, a.n_cu > 0 ? a.n_cu : 256)))
         return launch_wide_gemm(a, epi, s);
     // a SwiGLU launch streams the gate and the up rows: 2N weight rows
     const int NW = fast_gemm_waves(a.M, epi == FEPI_SWIGLU ? 2 * a.N : a.N, a.K, a.S, a.n_cu > 0 ? a.n_cu : 256);

@@ -330,8 +330,8 @@ static void launch_wide_cfg(const FastGemmArgs& a, int epi, hipStream_t s) {
         case FEPI_PART: hipLaunchKernelGGL((wide_gemm_kernel<MT, NT, WN, FEPI_PART>), g, b, 0, s, a, nfb, nrb); break;
         case FEPI_TOP2: hipLaunchKernelGGL((wide_gemm_kernel<MT, NT, WN, FEPI_TOP2>), g, b, 0, s, a, nfb, nrb); break;
         case FEPI_F32: hipLaunchKernelGGL((wide_gemm_kernel<MT, NT, WN, FEPI_F32>), g, b, 0, s, a, nfb, nrb); break;
-        default:
-            if constexpr (WN == 2)
+        case FEPI_SWIGLU:
+            if constexpr (WN == 2)  // (the choice for pairs)
                 hipLaunchKernelGGL((wide_gemm_kernel<MT, NT, WN, FEPI_SWIGLU>), g, b, 0, s, a, nfb, nrb);
             break;
     }
@@ -357,6 +357,7 @@ static void launch_wide_mt(const FastGemmArgs& a, int epi, const WideLaunch& c, 
 
 hipError_t launch_wide_gemm(const FastGemmArgs& a, int epi, hipStream_t s) {
     if (a.M < 1 || a.M > 256 || a.K % 128) return hipErrorInvalidValue;
+    if (epi != FEPI_PART && epi != FEPI_F32 && epi != FEPI_TOP2 && epi != FEPI_SWIGLU) return hipErrorInvalidValue;
     // a SwiGLU launch streams the gate and the up rows: 2N weight rows
     const bool pairs = epi == FEPI_SWIGLU;
     const WideLaunch c = wide_choose(a.M, pairs ? 2 * a.N : a.N, a.K, a.S, pairs, a.n_cu > 0 ? a.n_cu : 256);

@@ -1,5 +1,7 @@
 """Shared set-up of the GPU parity tests: one synthetic model fed to both the HIP engine and
 the CPU oracle (same weight bytes, same page table), and state copies between them."""
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -10,6 +12,23 @@ from paper_2605_30218_amd.runtime import GatedDecoder, prefill_rows
 
 def u16(t: torch.Tensor) -> np.ndarray:
     return t.cpu().numpy().view(np.uint16)
+
+
+class FastGemmArgs(C.Structure):
+    """mg::FastGemmArgs of csrc/mg_kernels.h, for the launchers that no C call reaches in every form."""
+    _fields_ = [("X", C.c_void_p), ("M", C.c_int), ("K", C.c_int), ("W", C.c_void_p * 3), ("bias", C.c_void_p * 3),
+                ("Nseg", C.c_int * 3), ("N", C.c_int), ("Y", C.c_void_p), ("part", C.c_void_p), ("S", C.c_int),
+                ("n_cu", C.c_int)]
+
+
+FEPI_BF16 = 0
+
+
+def fast_gemm_launcher(name):
+    """mg::launch_fast_gemm or mg::launch_wide_gemm: (args, epilogue, stream) -> hipError_t."""
+    f = getattr(mg.load(), f"_ZN2mg{len(name)}{name}ERKNS_12FastGemmArgsEiP12ihipStream_t")
+    f.argtypes, f.restype = [C.c_void_p, C.c_int, C.c_void_p], C.c_int
+    return lambda a, epi, stream=None: f(C.byref(a), epi, stream)
 
 
 class Pair:

@@ -146,6 +146,15 @@ def test_unsplit_outputs_of_few_features():
     assert [four_wave(n, N) for n, N in [(17, 4096), (32, 4096), (33, 6144), (64, 8192)]] == [False] * 4
 
 
+def test_wide_gemm_refuses_the_epilogue_it_does_not_have():
+    """The wide kernel has no bf16 epilogue: it says so (hipErrorInvalidValue, nothing launched)."""
+    from _gpu_common import FEPI_BF16, FastGemmArgs, fast_gemm_launcher
+    for M, N in [(65, 64), (128, 4096), (256, 16)]:
+        a = FastGemmArgs(M=M, K=256, N=N, S=1, n_cu=256)
+        a.Nseg[0] = N
+        assert fast_gemm_launcher("launch_wide_gemm")(a, FEPI_BF16) == 1
+
+
 def test_canon_gemv_launch_rule():
     """The verifier's canonical GEMV launch, host logic only: the vector-fma kernel up to 8
     rows, the matrix-core kernel above; one 16-row tile up to 16 rows and from 25 to 48, a

@@ -9,7 +9,7 @@ import torch
 from oracle import mgo
 from paper_2605_30218_amd import mg, synth
 
-from _gpu_common import Pair, dev_i32, u16
+from _gpu_common import FEPI_BF16, FastGemmArgs, Pair, dev_i32, fast_gemm_launcher, u16
 
 pytestmark = pytest.mark.gpu
 
@@ -38,6 +38,28 @@ def test_few_features_at_up_to_64_rows(n, N):
     Y = mg.op_linear(False, to_dev(X), to_dev(W)).cpu().numpy()
     ref = mgo.f32_from_bf16(X).astype(np.float64) @ mgo.f32_from_bf16(W).astype(np.float64).T
     np.testing.assert_array_equal(Y, ref.astype(np.float32))
+
+
+@pytest.mark.parametrize("n", [17, 64, 65, 128, 129, 251])
+@pytest.mark.parametrize("Nseg", [(16, 0, 0), (4096, 48, 16)])
+def test_bf16_epilogue_at_every_row_count(n, Nseg):
+    """The bf16 epilogue with its bias, which the wide kernel does not have, is computed above 64 rows
+    too.  Small integers: the sum is exact, so the result is its bf16 rounding."""
+    K, N = 256, sum(Nseg)
+    X, W = synth.small_int_bf16((n, K), seed=n), synth.small_int_bf16((N, K), seed=N)
+    b = synth.small_int_bf16((N,), seed=N + 1)
+    x, w, bias, y = to_dev(X), to_dev(W), to_dev(b), torch.zeros((n, N), dtype=torch.int16, device="cuda")
+    a = FastGemmArgs(X=x.data_ptr(), M=n, K=K, N=N, Y=y.data_ptr(), S=1, n_cu=256)
+    j = 0
+    for k, seg in enumerate(Nseg):
+        a.Nseg[k] = seg
+        if seg:
+            a.W[k], a.bias[k] = w[j:].data_ptr(), bias[j:].data_ptr()
+        j += seg
+    assert fast_gemm_launcher("launch_fast_gemm")(a, FEPI_BF16, torch.cuda.current_stream().cuda_stream) == 0
+    ref = mgo.f32_from_bf16(X).astype(np.float64) @ mgo.f32_from_bf16(W).astype(np.float64).T + mgo.f32_from_bf16(b)
+    want = torch.as_tensor(ref.astype(np.float32)).to(torch.bfloat16).view(torch.int16)
+    assert torch.equal(y.cpu(), want)
 
 
 @pytest.mark.parametrize("F", [128, 400, 1024])
