@@ -26,7 +26,7 @@ constexpr size_t ALIGN = 256;
 size_t up(size_t x) { return (x + ALIGN - 1) / ALIGN * ALIGN; }
 
 struct Plan {
-    size_t rope, x, h, qkv, qrot, att, act, attn_part, itab, gemm_part, top2_ws, top2_cnt, vlog, vrows, total;
+    size_t top2_cnt, rope, x, h, qkv, qrot, att, act, attn_part, itab, gemm_part, top2_ws, vlog, vrows, total;
     int rows_cap, max_pos, chunks_canon;
 };
 
@@ -67,6 +67,9 @@ Plan make_plan(const mg_model_cfg* c, int n_cu) {
     p.chunks_canon = (p.max_pos + CANON_CHUNK - 1) / CANON_CHUNK;
     const size_t R = p.rows_cap;
     size_t o = 0;
+    // what must keep its value between calls comes first: the gate's counters in front, where every
+    // shape has them, so that contexts that take turns on one workspace leave them alone
+    p.top2_cnt = o; o += up(TOP2_COUNTERS * sizeof(unsigned));
     p.rope = o; o += up((size_t)p.max_pos * hd * sizeof(float));
     p.x = o; o += up(R * d * 2);
     p.h = o; o += up(R * d * 2);
@@ -92,7 +95,6 @@ Plan make_plan(const mg_model_cfg* c, int n_cu) {
         }
     p.gemm_part = o; o += up((gp ? gp : 1) * sizeof(float));
     p.top2_ws = o; o += up(TOP2_WS_BYTES);
-    p.top2_cnt = o; o += up(TOP2_COUNTERS * sizeof(unsigned));
     p.vlog = o; o += up((size_t)c->max_batch * c->vocab * sizeof(float));
     // the matrix-core verifier's compact rows: token, position, page-table row, and the
     // top-2 pass's margin / gate / row list / count

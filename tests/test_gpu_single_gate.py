@@ -8,7 +8,9 @@ import pytest
 import torch
 
 from oracle import mgo
-from paper_2605_30218_amd import mg
+from paper_2605_30218_amd import mg, synth
+
+from _gpu_common import dev_i32
 
 pytestmark = pytest.mark.gpu
 
@@ -111,3 +113,30 @@ def test_launches_in_a_graph(B, V, launches):
         torch.cuda.synchronize()
         check(out, L[k], None, 0.3)
     assert hip.hipGraphExecDestroy(run) == 0 and hip.hipGraphDestroy(graph) == 0
+
+
+def test_contexts_that_take_turns_on_one_workspace():
+    """Two contexts of one model for different batches over the same workspace, used in turn: neither's
+    scratch is where the other keeps its gate's counters (a counter that is overwritten would leave the
+    gate's outputs as they were)."""
+    s = synth.TINY
+    ws = synth.make_weights(s, seed=2)
+    big, pages = 64, 4
+    pt, n_pages = synth.make_page_table([16 * pages] * big, s.page_size, pages, seed=3)
+    # (2 items of prefill: the small context's plan then ends inside the normalised rows of the big one's step)
+    engs = [mg.Engine(s, ws, b, pages, n_pages, max_prefill=m) for b, m in ((big, 0), (2, 2))]
+    assert engs[0].workspace.numel() >= engs[1].workspace.numel()
+    lib, small = engs[1].lib, engs[1]
+    lib.mg_destroy(small.ctx)
+    assert lib.mg_create(ctypes.byref(small.cfg), small._wtab, small.kv_pool.data_ptr(), small.kv_pool.numel() * 2,
+                         engs[0].workspace.data_ptr(), small.workspace.numel(), ctypes.byref(small.ctx)) == 0
+    tok, pos, ptd = dev_i32(np.arange(big) % s.vocab), dev_i32(np.full(big, 16 * pages - 1)), dev_i32(pt)
+    for rnd in range(3):
+        for e, B in zip(engs, (big, 2)):
+            lg = torch.empty((B, s.vocab), dtype=torch.float32, device="cuda")
+            e.decode_step(B, tok, pos, ptd, lg)
+            for f, n in zip(engs, (B, min(B, 2))):  # either context's gate after either one's step
+                out = outputs(n)
+                f.margin_gate(n, lg, None, 0.3, *out)
+                torch.cuda.synchronize()
+                check(out, lg[:n].cpu().numpy(), None, 0.3)
