@@ -25,9 +25,12 @@ import os
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-# kernel name prefix -> source files (bench names: fast_gemm, canon_gemv; the canonical GEMV
-# has a vector-fma kernel and a matrix-core kernel, canon_gemv_kernel and canon_gemv_mfma_kernel)
-SOURCES = {"fast_gemm": ("k_gemm.hip",), "canon_gemv": ("k_gemv.hip", "k_gemv_mfma.hip")}
+# kernel class (bench names: fast_gemm, canon_gemv) -> source files, and -> its kernels: the fast
+# projections have one for up to 64 rows and one above, the canonical GEMV a vector-fma kernel and a
+# matrix-core kernel
+SOURCES = {"fast_gemm": ("k_gemm.hip", "k_gemm_wide.hip"), "canon_gemv": ("k_gemv.hip", "k_gemv_mfma.hip")}
+KERNELS = {"fast_gemm": ("fast_gemm_kernel", "wide_gemm_kernel"),
+           "canon_gemv": ("canon_gemv_kernel", "canon_gemv_mfma_kernel")}
 DECODE_START = "resid_norm_kernel"
 
 
@@ -46,24 +49,29 @@ def _decode_window(rows, key):
     return rows
 
 
+def _is(kernel: str, name: str) -> bool:
+    """Whether a dispatch of kernel `name` belongs to `kernel`: a class of KERNELS, or (part of) a kernel's name."""
+    return any(k in name for k in KERNELS.get(kernel, (kernel,)))
+
+
 def _short(name: str) -> str:
     n = name.split("(")[0]
     return n.replace("void ", "").replace("mg::", "")
 
 
-MODE_KERNELS = ("fast_gemm_kernel", "canon_gemv", "attn_fast_fused_kernel", "attn_canon_kernel")
+MODE_KERNELS = ("fast_gemm_kernel", "wide_gemm_kernel", "canon_gemv", "attn_fast_fused_kernel", "attn_canon_kernel")
 
 
 def _mode_tables(rows, modes):
     cuts = [i for i, r in enumerate(rows) if "copyBuffer" in r["Kernel_Name"]
             and int(r["End_Timestamp"]) - int(r["Start_Timestamp"]) > 1_000_000]
     bounds = [0] + cuts + [len(rows)]
-    # windows that run decode steps (copies after the last mode, e.g. for the CPU baseline,
-    # leave windows without any); the modes are the last of them, before them the quantile
+    # windows that run decode steps, all of which run a fast projection (copies after the last mode,
+    # e.g. for the CPU baseline, leave windows without any); the modes are the last of them, before them the quantile
     # tau calibration and the runs of the threshold recipe (reference decode, fast run, one
     # run per tau)
     segs = [rows[bounds[w]:bounds[w + 1]] for w in range(len(bounds) - 1)]
-    segs = [seg for seg in segs if any(MODE_KERNELS[0] in r["Kernel_Name"] for r in seg)]
+    segs = [seg for seg in segs if any(_is("fast_gemm", r["Kernel_Name"]) for r in seg)]
     nrec = max(0, len(segs) - 1 - len(modes))
     names = ["tau calibration"] + [f"recipe run {k}" for k in range(1, nrec + 1)] + modes
     lines = ["", "per mode (windows split at the KV snapshot restores; warmup steps included):",
@@ -71,7 +79,7 @@ def _mode_tables(rows, modes):
     for w in range(min(len(names), len(segs))):
         seg = segs[w]
         for kn in MODE_KERNELS:
-            d = [int(r["End_Timestamp"]) - int(r["Start_Timestamp"]) for r in seg if kn in r["Kernel_Name"]]
+            d = [int(r["End_Timestamp"]) - int(r["Start_Timestamp"]) for r in seg if _is(kn, r["Kernel_Name"])]
             if d:
                 lines.append(f"{names[w]:16s} {kn:22s} {len(d):7d} {sum(d) / len(d) / 1e3:9.1f} {sum(d) / 1e6:9.2f}")
     return lines
@@ -96,11 +104,11 @@ def trace(trace_csv: str, out: str, command: str, modes: str = "") -> None:
     lines += ["", "per launch shape (grid x,y,z in threads) of the weight-streaming kernels:",
               f"{'kernel':44s} {'grid':>22s} {'calls':>7s} {'avg_us':>9s}"]
     for (k, g), v in sorted(shape.items(), key=lambda kv: -sum(kv[1])):
-        if "fast_gemm" in k or "canon_gemv" in k:
+        if any(_is(kind, k) for kind in KERNELS):
             lines.append(f"{k[:44]:44s} {','.join(g):>22s} {len(v):7d} {sum(v) / len(v) / 1e3:9.1f}")
     lines.append("")
     for kn in SOURCES:
-        fg = [d for k, v in by.items() if k.startswith(kn) for d in v]
+        fg = [d for k, v in by.items() if _is(kn, k) for d in v]
         if fg:
             lines.append(f"{kn} kernels, all shapes: {len(fg)} launches, average {sum(fg) / len(fg) / 1e3:.1f} us")
     if modes:
@@ -113,7 +121,7 @@ def _per_dispatch(path: str, filt: str, window: bool = True):
     rows = list(csv.DictReader(open(path)))
     rows = _decode_window(rows, "Dispatch_Id") if window else rows
     for r in rows:
-        if filt in r["Kernel_Name"]:
+        if _is(filt, r["Kernel_Name"]):
             out[int(r["Grid_Size"])].append(float(r["Counter_Value"]) * 1024.0)
     return out
 
@@ -151,7 +159,7 @@ def util(pmc_csv: str, out: str, command: str, kernels: str) -> None:
     names = kernels.split(",")
     for r in rows:
         for k in names:
-            if k in r["Kernel_Name"]:
+            if _is(k, r["Kernel_Name"]):
                 agg[k][r["Counter_Name"]].append(float(r["Counter_Value"]))
     counters = sorted({c for k in agg for c in agg[k]})
     lines = [f"command: {command}", "window: decode steps; mean over each kernel's dispatches", "",
@@ -179,7 +187,7 @@ def shapes(pmc_csvs: str, out: str, command: str, kernels: str) -> None:
         seen = set()
         for r in rows:
             kn = r["Kernel_Name"]
-            if not any(k in kn for k in names):
+            if not any(_is(k, kn) for k in names):
                 continue
             key = (kn.replace("void ", "").replace("mg::", "").split("(")[0], int(r["Grid_Size"]))
             cnt[key][r["Counter_Name"]].append(float(r["Counter_Value"]))

@@ -55,6 +55,51 @@ def test_trace_mode_windows_are_named_from_the_last_decode_windows():
     assert ("recipe run 1", "canon_gemv") in got
 
 
+def test_summaries_know_both_fast_projection_kernels(tmp_path):
+    """A workload above 64 rows runs its fast projections on the wide kernel alone: it is in the mode
+    table, the shape table, the class average and the traffic of fast_gemm, whose source hash covers
+    both kernels' files."""
+    from paper_2605_30218_amd import profsum
+    wide = "void mg::wide_gemm_kernel<2, 4, 2, 1>(mg::FastGemmArgs, int, int)"
+    head = "Kernel_Name,Start_Timestamp,End_Timestamp,Grid_Size_X,Grid_Size_Y,Grid_Size_Z"
+    rows, t = [head], 0
+
+    def row(name, dur, grid="16384,4,1"):
+        nonlocal t
+        t += 5_000_000
+        rows.append(f'"{name}",{t},{t + dur},{grid}')
+
+    row("mg::resid_norm_kernel(int)", 5_000)
+    row(wide, 40_000)                                   # tau calibration
+    row("__amd_rocclr_copyBuffer", 2_000_000)
+    row(wide, 60_000)                                   # off
+    row("__amd_rocclr_copyBuffer", 2_000_000)
+    row(wide, 80_000)                                   # gated
+    row("mg::canon_gemv_mfma_kernel<8>(mg::GemvArgs)", 30_000, "131072,1,1")
+    (tmp_path / "t.csv").write_text("\n".join(rows) + "\n")
+    profsum.trace(str(tmp_path / "t.csv"), str(tmp_path / "t.txt"), "cmd", "off,gated")
+    out = (tmp_path / "t.txt").read_text()
+    assert "fast_gemm kernels, all shapes: 3 launches, average 60.0 us" in out
+    assert "canon_gemv kernels, all shapes: 1 launches, average 30.0 us" in out
+    shapes = out[out.index("per launch shape"):out.index("fast_gemm kernels, all shapes")]
+    assert "wide_gemm_kernel<2, 4, 2, 1>" in shapes and "16384,4,1" in shapes
+    modes = out[out.index("per mode"):].splitlines()
+    got = {(ln[:16].strip(), ln[17:39].strip()): float(ln.split()[-2]) for ln in modes[2:]}
+    assert got[("off", "wide_gemm_kernel")] == 60.0 and got[("gated", "wide_gemm_kernel")] == 80.0
+    assert got[("tau calibration", "wide_gemm_kernel")] == 40.0 and got[("gated", "canon_gemv")] == 30.0
+
+    pmc = "Dispatch_Id,Kernel_Name,Grid_Size,Counter_Name,Counter_Value\n"
+    for name, val in (("f", 100.0), ("w", 10.0)):
+        (tmp_path / f"{name}.csv").write_text(pmc + f'1,resid_norm_kernel,64,C,1\n2,"{wide}",65536,C,{val}\n'
+                                              f"3,fast_gemm_kernel<4>,65536,C,{val}\n4,attn_canon_kernel,64,C,9\n")
+    (tmp_path / "c.csv").write_text(pmc + "1,copy16_kernel,64,C,1\n2,copy16_kernel,64,C,1\n")
+    c = str(tmp_path / "c.csv")
+    profsum.traffic("fast_gemm", str(tmp_path / "f.csv"), str(tmp_path / "w.csv"), c, c, 1024, str(tmp_path / "o.txt"), "a", "b")
+    per, sha = profsum.read_traffic(str(tmp_path / "o.txt"))
+    assert per == 110 * 1024 and sha == profsum.source_sha("fast_gemm")
+    assert set(profsum.SOURCES["fast_gemm"]) == {"k_gemm.hip", "k_gemm_wide.hip"}
+
+
 def test_forward_bytes_of_the_llama8b_shape():
     """The benchmark's algorithmic bytes: 7.505 B streamed parameters (embedding gathered, not
     streamed) and 128 KiB of K/V per token over all layers on the Llama-3.1-8B shape."""
