@@ -1,7 +1,7 @@
 """The fast path's projection above 64 rows (K % 128 == 0) at the edges of its tiles: row counts
 around the 64-row blocks, feature counts around 16-feature tiles and narrow blocks, one and
-several 128-element units of K, split K, and the SwiGLU and top-2 epilogues against batches
-small enough for the other kernel (the same order of every sum, so the same bits)."""
+several 128-element units of K, split K, and the SwiGLU, fp32 and top-2 epilogues against groups of
+16 rows, which only the other kernel takes (the same order of every sum, so the same bits)."""
 import numpy as np
 import pytest
 import torch
@@ -65,7 +65,8 @@ def test_bf16_epilogue_at_every_row_count(n, Nseg):
 @pytest.mark.parametrize("F", [128, 400, 1024])
 def test_matrix_core_verifier_bits_across_the_kernels(F):
     """The matrix-core verifier's logits, tokens and columns for n rows at once are those of the
-    rows in groups of 20 (the kernel for up to 64 rows), with the logits and without."""
+    rows in groups of 16, with the logits and without; the groups' tokens come from the other
+    kernel's top-2 epilogue, and equal those of its logits.  At 33 rows only the LM head is wide."""
     s = synth.ModelShape("wide", 2, 384, 6, 2, 64, F, 1040, True, 1e4, 1e-5)
     B = 201
     pair = Pair(s, max_batch=B, ctx_cap=48, seed=F)
@@ -84,9 +85,12 @@ def test_matrix_core_verifier_bits_across_the_kernels(F):
         torch.cuda.synchronize()
         return (lg.cpu().numpy().view(np.uint32) if logits else np.zeros((n, 1))), vt.cpu().numpy(), u16(vc)
 
-    parts = [run(np.arange(r, min(r + 20, B)), True) for r in range(0, B, 20)]
+    groups = [np.arange(r, min(r + 16, B)) for r in range(0, B, 16)]
+    parts = [run(g, True) for g in groups]
     want = [np.concatenate([p[k] for p in parts]) for k in range(3)]
-    for n in (65, 100, 130, B):
+    np.testing.assert_array_equal(np.concatenate([run(g, False)[1] for g in groups]), want[1])
+    np.testing.assert_array_equal(want[1], want[0].view(np.float32).argmax(1))
+    for n in (33, 65, 100, 130, B):
         for logits in (True, False):
             got = run(np.arange(n), logits)
             if logits:
