@@ -32,10 +32,11 @@
 // What bounds it: the K/V stream.  The vector-ALU P V product of the kernel before this one
 // (8 fma and a shuffle per head and position group, two blocks per KV head above 4 heads) took
 // about as long as the stream itself.  Per layer, before and after: 128 rows of 128..2048
-// positions, 8 KV heads of 5 query heads, 183 and 122 us (4.7 TB/s); 251 rows of 40..700
-// positions, 4 of 7, 79 and 63; 64 rows of 512..768, 8 of 4, 41 and 37 (4.5 TB/s); 9 rows of
-// 4096..16384, 85 and 79.  The steady stream runs at 5.5 TB/s (6.1: a plain read); 8 us of
-// each launch are its dependent first loads (position, page, K/V) and the merge.
+// positions, 8 KV heads of 5 query heads, 167 and 108 us (5.3 TB/s); 251 rows of 40..700
+// positions, 4 of 7, 79 and 59; 64 rows of 512..768, 8 of 4, 40 and 34 (4.9 TB/s); 9 rows of
+// 4096..16384, with the merge, 97 and 81; one row of 512, 19 (with its merge) and 11.  The steady
+// stream runs at 5.5 TB/s (6.1: a plain read); 8 us of each launch are its dependent first loads
+// (position, page, K/V) and the merge.
 // Epilogue: each wave's (m, l, O) goes to LDS; position p contributes its own partial
 // (m = score of q' . k'_p, l = 1, O = v_p) in split 0; the partials are merged and
 // out = bf16(O / L), or the split's merged partial is stored for the split merge.  Every
@@ -66,7 +67,7 @@ __device__ __forceinline__ float fa_scale(int hd) { return hd == 128 ? 0x1.6a09e
 __device__ __forceinline__ uint32_t top_halves(float lo, float hi) {
     return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
 }
-// NW words that no other block reads, with the "nt" policy where NTP
+// NW words of the K/V stream, with the "nt" policy where NTP
 template <class T, int NW, bool NTP>
 __device__ __forceinline__ T kv_load(const uint16_t* p) {
     using v = uint32_t __attribute__((ext_vector_type(NW)));
@@ -503,9 +504,12 @@ hipError_t launch_fast_attention(const FastAttnArgs& args, hipStream_t s) {
     a.longest_first = a.nsplit == 1 && units > 2 * (a.n_cu > 0 ? a.n_cu : 256);
     const dim3 grid(units, 1, a.nsplit);
     // Launches of a block per CU and more are bound by the K/V stream, which then goes past the
-    // caches' replacement ("nt": 128 rows of 128..2048 positions 109 us a layer against 122 with the default
-    // policy, 64 rows of 512..768 33.6 against 37.2); smaller ones wait for single loads, which
-    // the caches may still hold (one row of 512 positions: 13.9 against 13.0)
+    // caches' replacement ("nt": 128 rows of 128..2048 positions 108 us a layer against 121 with the default
+    // policy, 64 rows of 512..768 34 against 36); smaller ones wait for single loads, which
+    // the caches may still hold (one row of 512 positions: 13.9 against 13.0).  Pages that rows
+    // share are read by each row's blocks, from the caches if they are kept there: a two-layer step of 32
+    // or 64 rows on one prefix of 512 to 4096 positions is 3 to 5% slower with the policy, of
+    // 128 rows on 1024 2% faster; which pages are shared stands in device memory only
     const bool stream = (long)units * a.nsplit >= (a.n_cu > 0 ? a.n_cu : 256);
     if (a.m.hd == 128)
         launch_hd<128>(a, G, grid, stream, s);
@@ -519,7 +523,10 @@ int fast_attn_splits(int rows, int n_kv_heads, int max_pages_per_row, int n_cu, 
     const int blocks = rows * n_kv_heads;
     if (blocks <= 0 || blocks >= 2 * n_cu) return 1;  // enough blocks: one per (row, KV head)
     // short rows: a split saves less than the merge launch costs (one row of 512 positions, 8 KV
-    // heads: 13.0 us in one block per KV head, 10.7 in two and 4.7 for the merge)
+    // heads: 13.0 us in one block per KV head, 10.7 in two and 4.7 for the merge).  With 48 to 63 pages
+    // of capacity rows that fill it would gain 1 to 3% of a two-layer step in splits at up to 16
+    // rows, but rows at a quarter of it lose 2 to 3%, 32 rows lose 1 to 4% at any length and 17 rows of the
+    // matrix-core verifier (whose split is that of 32) 5 to 7%
     if (max_pages_per_row < 64) return 1;
     int ns = (2 * n_cu + blocks - 1) / blocks;
     ns = ns < max_pages_per_row / 16 ? ns : max_pages_per_row / 16;

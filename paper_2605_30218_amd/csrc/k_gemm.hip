@@ -11,10 +11,11 @@
 //    stages (two chunks ahead), the activations through a block-wide double buffer --
 //    in a swizzled layout whose loads read each row's chunk as one contiguous run and
 //    whose MFMA fragment reads are free of bank conflicts (see issue_w_lds).
-//  * otherwise (above 64 rows only K % 128 != 0: k_gemm_wide.hip takes the rest): weights straight from HBM into MFMA B-operand registers (lane (j, q)
-//    loads W[n+j][k+8q .. k+8q+7], 16 rows x 64 contiguous bytes per k step of 16
-//    features) in a ping-pong register pair, the activations staged through a
-//    double-buffered, padded LDS tile.  Loads complete in order, so staging the
+//  * otherwise (above 64 rows only K % 128 != 0: k_gemm_wide.hip takes the rest): weights
+//    straight from HBM into MFMA B-operand registers (lane (j, q) loads
+//    W[n+j][k+8q .. k+8q+7], 16 rows x 64 contiguous bytes per k step of 16 features) in a
+//    ping-pong register pair, the activations staged through a double-buffered, padded LDS
+//    tile.  Loads complete in order, so staging the
 //    activations of chunk c+1 waits only for those, and the weights of chunk c+1 stay
 //    in flight across the barrier.  Every load is unconditional (rows past N read row
 //    0, k past K reads the row's last group; the activations there are zero and the

@@ -6,9 +6,11 @@
 // from LDS for 16 features, and above 64 rows those reads, not the weight stream, set the
 // time.  Here a block owns BM = 64 MT rows x BN = 16 NT WN features as 4 x WN waves of MT x NT
 // tiles, so an operand read serves MT or NT MFMAs: with WN = 2 the LDS reads per k-step of 32
-// are 8 (MT + NT) KiB for 8 MT NT MFMAs.  The rows may be split over blocks as well (row blocks
-// of one feature block are neighbours on one XCD, so the weights come from HBM once): a launch
-// with few features fills the chip so without the traffic of split-K partial tiles.
+// are 8 (MT + NT) KiB for 8 MT NT MFMAs.  The rows may be split over blocks as well: a launch
+// with few features fills the chip so without the traffic of split-K partial tiles.  Row blocks
+// of one feature block are neighbours on one XCD, so the weights come from HBM once (6144 and 4096 x
+// 4096 in two row blocks at 128 rows and four at 251: a launch fetches the weights' bytes, and
+// the activations' once per XCD).
 // Both operands go through LDS in chunks of 64 elements by direct-to-LDS loads, D stages in
 // a ring (D - 1 chunks requested ahead).  A load moves 8 rows x 128 contiguous bytes; the
 // 16-byte piece G of stage row r sits at slot 8 r + (G xor (r mod 8)), so the 16 rows that an MFMA
@@ -52,7 +54,7 @@ template <int OFF>
 __device__ __forceinline__ void wg_read(u32x4_w& v, uint32_t addr) {
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(OFF));
 }
-// 64 x 16 bytes, lane i to slot i; AUX: cache policy (MG_AUX_NT: streamed, no reuse)
+// 64 x 16 bytes, lane i to slot i; AUX: cache policy
 template <int AUX>
 __device__ __forceinline__ void wg_load(const uint16_t* src, unsigned char* slots) {
     __builtin_amdgcn_global_load_lds(src, slots, 16, 0, AUX);
@@ -109,6 +111,10 @@ __global__ __launch_bounds__(256 * WN, 2) void wide_gemm_kernel(FastGemmArgs a, 
             wsrc[t] = a.W[seg] + (size_t)n * K + lp;
         }
     }
+    // The weights are streamed ("nt") with several row blocks too: those run together and fetch no
+    // more than with the default policy, which is 1 to 5% slower on the O and QKV shapes of 65 to
+    // 256 rows.  The exception is a row block of 128 next to one at most half full, which runs ahead: 3 to 6%
+    // of the weights are fetched again (4096 x 14336 at 192 rows 46 us, 43 with the default policy).
     auto issue = [&](int c, int stage) {
         unsigned char* buf = ring + stage * S::STAGE + 1024 * wave;
         const size_t k = (size_t)c * WG_KC;

@@ -103,7 +103,10 @@ __device__ __forceinline__ void gemv_store_x(float4 (*xs)[2][64], int wave, int 
 }
 
 // weights of group g (clamped to the last group) of the J feature rows, streamed ("nt" policy: at 5
-// rows the 4096 x 14336 down projection 27.8 us against 30.6, O 11.6 against 12.5)
+// rows the 4096 x 14336 down projection 27.8 us against 30.6, O 11.6 against 12.5).  Two row tiles
+// (a device count with a capacity of 17 to 24) read each weight twice: a two-layer verifier call of such a
+// capacity is 1 to 3% faster with the policy at up to half the capacity and 1 to 2% slower when it
+// is full (20 of 20 rows, 5120 features: 753 us against 746)
 template <int J>
 __device__ __forceinline__ void gemv_load_w(const uint16_t* const (&wrow)[J], int g, int G, uint4 (&w)[J]) {
     const int gc = min(g, G - 1);

@@ -56,9 +56,10 @@ __device__ __forceinline__ float canon_exp(float x) {
 __device__ __forceinline__ float ieee_div(float a, float b) { return a / b; }
 __device__ __forceinline__ float ieee_sqrt(float a) { return __builtin_sqrtf(a); }
 
-// Cache policy of a direct-to-LDS load (its aux operand) whose data no other block reads: "nt", so
-// that streamed weights do not push the activations and partial tiles out of the L2s.  Streaming alone, the
-// gate/up weights of 128 rows (283 MB) took 50.6 us so and 55.0 with the default policy.
+// Cache policy of a direct-to-LDS load (its aux operand) of streamed data: "nt", so that weights do
+// not push the activations and partial tiles out of the L2s.  Blocks that read the same data at about the
+// same time still meet in their L2.  Streaming alone, the gate/up weights of 128 rows (283 MB) took
+// 50.6 us so and 55.0 with the default policy.
 constexpr int MG_AUX_NT = 2;
 
 // xor butterfly over the 64 lanes: a_l <- a_l + a_(l xor o), o = 32..1.
