@@ -101,26 +101,45 @@ __global__ __launch_bounds__(FA_THREADS) __attribute__((amdgpu_waves_per_eu(MG_F
     __shared__ __attribute__((aligned(16))) float wo[FA_WAVES][NC][HD];
 
     const int kh = blockIdx.x % m.Hkv, split = blockIdx.z;
-    int r = blockIdx.x / m.Hkv;
+    int r = blockIdx.x / m.Hkv, p;
     if (a.longest_first) {
         // blocks are dispatched in index order: block index u / Hkv takes the row whose context
         // is the (u / Hkv)-th longest (ties by row), so that no long row starts when the others
-        // are nearly done.  Every block finds its row by counting, over all rows' positions.
-        int* ps_ = reinterpret_cast<int*>(&wo[0][0][0]);
-        static_assert(sizeof(wo) >= (FA_MAXB + 1) * sizeof(int), "positions and the row fit");
-        const int mine = t < a.B ? a.positions[t] : -1;
-        ps_[t] = mine;
-        __syncthreads();
-        int rank = 0;
-        for (int j = 0; j < a.B; ++j) {
-            const int o = ps_[j];
-            rank += (o > mine || (o == mine && j < t)) ? 1 : 0;
+        // are nearly done.  Every wave finds it from all rows' positions, row 64 k + lane in pos[k]:
+        // the position bit by bit from the count of rows at or above a candidate, then the row
+        // among those at that position, some 12 counts of 4 ballots.  (Each thread counting the rows
+        // before its own took all rows' compares on the vector ALUs in every block: two layers of 251
+        // rows at 40..700 positions and 4 KV heads 507 us with their projections, 485 so; of 200 rows at
+        // up to 100 positions and 8 KV heads 201 and 171.)
+        constexpr int NP = FA_MAXB / 64;
+        int pos[NP];
+#pragma unroll
+        for (int k = 0; k < NP; ++k) pos[k] = 64 * k + lane < a.B ? a.positions[64 * k + lane] : -1;
+        p = 0;
+        for (int bit = 31 - __builtin_clz(16 * m.max_pages_per_row); bit >= 0; --bit) {
+            const int cand = p | (1 << bit);
+            int cnt = 0;
+#pragma unroll
+            for (int k = 0; k < NP; ++k) cnt += __popcll(__ballot(pos[k] >= cand));
+            if (cnt > r) p = cand;
         }
-        if (t < a.B && rank == r) ps_[FA_MAXB] = t;
-        __syncthreads();
-        r = __builtin_amdgcn_readfirstlane(ps_[FA_MAXB]);
+        int n = r;  // the row's place among those at position p
+#pragma unroll
+        for (int k = 0; k < NP; ++k) n -= __popcll(__ballot(pos[k] > p));
+        r = 0;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const unsigned long long at = __ballot(pos[k] == p);
+            const int c = __popcll(at);
+            if (n >= 0 && n < c) {
+                const bool me = ((at >> lane) & 1) && __popcll(at & ((1ull << lane) - 1)) == n;
+                r = 64 * k + __ffsll(__ballot(me)) - 1;
+            }
+            n -= c;
+        }
+    } else {
+        p = a.positions[r];
     }
-    const int p = a.positions[r];
     const int32_t* ptab = a.page_table + (size_t)r * m.max_pages_per_row;
     const int npg = (p + 15) / 16;  // pages holding positions 0..p-1
     // this split's pages [pg0, pg1): a fixed share of the capacity, so a block's work is
@@ -499,9 +518,12 @@ hipError_t launch_fast_attention(const FastAttnArgs& args, hipStream_t s) {
     if (a.nsplit < 1 || a.split_pages < 1 || (long)a.nsplit * a.split_pages < a.m.max_pages_per_row ||
         (a.nsplit > 1 && !a.split_part))
         return hipErrorInvalidValue;
-    // more blocks than two per CU: the longest rows first
+    // more blocks than two per CU: the longest rows first, where rows can differ by more than finding
+    // them costs (two layers of 128 rows, 8 KV heads of 4 query heads, contexts of half to all of 2200
+    // positions 396 against 428 us in the rows' own order, of 500 179 against 182, but of 300 159
+    // against 154)
     const int units = a.B * a.m.Hkv;
-    a.longest_first = a.nsplit == 1 && units > 2 * (a.n_cu > 0 ? a.n_cu : 256);
+    a.longest_first = a.nsplit == 1 && units > 2 * (a.n_cu > 0 ? a.n_cu : 256) && a.m.max_pages_per_row >= 32;
     const dim3 grid(units, 1, a.nsplit);
     // Launches of a block per CU and more are bound by the K/V stream, which then goes past the
     // caches' replacement ("nt": 128 rows of 128..2048 positions 108 us a layer against 121 with the default

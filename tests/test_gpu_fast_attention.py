@@ -142,6 +142,11 @@ def test_an_infinity_in_v_reaches_the_gate_as_nan(value):
 
 
 @pytest.mark.parametrize("hd,G,B", [(64, 1, 256), (64, 6, 129), (128, 5, 131), (128, 4, 130), (128, 7, 133)])
-def test_longest_rows_first(hd, G, B):
+@pytest.mark.parametrize("cap,hi", [(128, 120), (512, 120), (528, 528)])
+def test_longest_rows_first(hd, G, B, cap, hi):
+    """512 positions of capacity and more: the longest first (many rows of equal length among them; and
+    1 to capacity positions); below, the rows' own order."""
     rng = np.random.RandomState(B)
-    check(hd, G, 4, [int(c) for c in rng.randint(1, 120, B)], 128)
+    ctx = [int(c) for c in rng.randint(1, hi, B)]
+    ctx[B // 2], ctx[B // 3] = hi, 1
+    check(hd, G, 4, ctx, cap)
