@@ -384,13 +384,14 @@ int top2_slices(int B, int V) {
 // slices of a single-launch gate, or 0: at most 64 (one row's states in one wave) and 256 states, no
 // slice more than 4 times as long as the two-launch form's (18 rows of 32000 in 8 instead of 32: 8.2 us
 // against 10.1) or above 4096 values (8 rows of 152064 in slices of 4752: 10.3 against 10.1), or above
-// 2048 where rows are not 16-byte multiples and are read by the word (8 rows of 128257 in slices of 4012:
-// 11.6 against 10.5, 4 rows in slices of 2008 10.3 against 10.5)
+// 3072 where rows are not 16-byte multiples and are read by the word (8 rows of 128257 in slices of 4012:
+// 11.6 against 10.5, 16 of 50257 in slices of 3144 10.9 against 10.5, 4 of 128257 in slices of 2008 10.3
+// against 10.5)
 static int top2_single_slices(int B, int V) {
     const int two = top2_slices(B, V);
     int nsl = two < 64 ? two : 64;
     while (nsl > 1 && nsl * B > 256) nsl /= 2;
-    return nsl * B <= 256 && nsl * 4 >= two && V <= (V % 4 ? 2048L : 4096L) * nsl ? nsl : 0;
+    return nsl * B <= 256 && nsl * 4 >= two && V <= (V % 4 ? 3072L : 4096L) * nsl ? nsl : 0;
 }
 
 size_t top2_ws_bytes(int B, int V) {
@@ -411,7 +412,8 @@ static bool stream_captures(hipStream_t s) {
 // values 7.5 against 7.7 us, 16 rows of 4096 6.4 against 6.6, 4 of 32000 7.1 against 7.3); above, it takes more (32 rows of
 // 4096 7.1 against 6.6, 64 of them 8.7 against 6.8, 8 of 128256 10.4 against 8.1) and pays only where the
 // host's launches set the time, which is a gate called by itself outside a graph (a call: 8.1 against 10.2
-// us, 8.5 against 10.3, 10.1 against 10.3), not the last step of a verifier call (alone = false).
+// us, 8.5 against 10.3, 10.1 against 10.3), not the last step of a verifier call (alone = false).  The same
+// for slices above 2048 values read by the word (one row of 152063 8.1 against 7.2 in a graph).
 hipError_t launch_top2(int B, int V, const float* logits, const uint8_t* prot, float tau, int32_t* top1, float* margin,
                        uint8_t* gate, int32_t* gated_rows, int32_t* n_gated, int32_t* n_gated_host, void* part_ws,
                        unsigned* counters, const int32_t* n_dev, bool alone, hipStream_t s) {
@@ -419,7 +421,8 @@ hipError_t launch_top2(int B, int V, const float* logits, const uint8_t* prot, f
     if (B > 256) return hipErrorInvalidValue;
     Top2* part = static_cast<Top2*>(part_ws);
     const int one = top2_single_slices(B, V);
-    if (one && (one * B <= 64 || (alone && !stream_captures(s)))) {
+    const bool even = one * B <= 64 && !(V % 4 && V > 2048L * one);
+    if (one && (even || (alone && !stream_captures(s)))) {
         const int slice = ((V + one - 1) / one + 3) & ~3;
         hipLaunchKernelGGL(top2_single_kernel, dim3(one, B), dim3(256), 0, s, B, V, slice, logits, part, one, counters,
                            prot, tau, top1, margin, gate, gated_rows, n_gated, n_gated_host, n_dev);
