@@ -32,9 +32,9 @@
 // What bounds it: the K/V stream.  The vector-ALU P V product of the kernel before this one
 // (8 fma and a shuffle per head and position group, two blocks per KV head above 4 heads) took
 // about as long as the stream itself.  Per layer, before and after: 128 rows of 128..2048
-// positions, 8 KV heads of 5 query heads, 167 and 108 us (5.3 TB/s); 251 rows of 40..700
-// positions, 4 of 7, 79 and 59; 64 rows of 512..768, 8 of 4, 40 and 34 (4.9 TB/s); 9 rows of
-// 4096..16384, with the merge, 97 and 81; one row of 512, 19 (with its merge) and 11.  The steady
+// positions, 8 KV heads of 5 query heads, 167 and 105 us (5.4 TB/s); 251 rows of 40..700
+// positions, 4 of 7, 78 and 48; 64 rows of 512..768, 8 of 4, 41 and 34 (4.9 TB/s); 9 rows of
+// 4096..16384, with the merge, 96 and 82; one row of 512, 19 (with its merge) and 11.  The steady
 // stream runs at 5.5 TB/s (6.1: a plain read); 8 us of each launch are its dependent first loads
 // (position, page, K/V) and the merge.
 // Epilogue: each wave's (m, l, O) goes to LDS; position p contributes its own partial
@@ -527,7 +527,7 @@ hipError_t launch_fast_attention(const FastAttnArgs& args, hipStream_t s) {
     const dim3 grid(units, 1, a.nsplit);
     // Launches of a block per CU and more are bound by the K/V stream, which then goes past the
     // caches' replacement ("nt": 128 rows of 128..2048 positions 108 us a layer against 121 with the default
-    // policy, 64 rows of 512..768 34 against 36); smaller ones wait for single loads, which
+    // policy, 4 us of each for an earlier row search; 64 rows of 512..768 34 against 36); smaller ones wait for single loads, which
     // the caches may still hold (one row of 512 positions: 13.9 against 13.0).  Pages that rows
     // share are read by each row's blocks, from the caches if they are kept there: a two-layer step of 32
     // or 64 rows on one prefix of 512 to 4096 positions is 3 to 5% slower with the policy, of
