@@ -383,15 +383,16 @@ int top2_slices(int B, int V) {
 
 // slices of a single-launch gate, or 0: at most 64 (one row's states in one wave) and 256 states, no
 // slice more than 4 times as long as the two-launch form's (18 rows of 32000 in 8 instead of 32: 8.2 us
-// against 10.1) or above 4096 values (8 rows of 152064 in slices of 4752: 10.3 against 10.1), or above
-// 3072 where rows are not 16-byte multiples and are read by the word (8 rows of 128257 in slices of 4012:
-// 11.6 against 10.5, 16 of 50257 in slices of 3144 10.9 against 10.5, 4 of 128257 in slices of 2008 10.3
-// against 10.5)
+// against 10.1) or above 4096 values (8 rows of 152064 in slices of 4752: 10.3 against 10.1).  Rows that
+// are not 16-byte multiples are read by the word, which takes about 5.4 us + 13.7 ns a state + 0.66 ns a
+// value of a slice (8 rows of 128257, 256 states of 4012: 11.6; 6 rows 10.7; 16 of 50257, 256 of 3144: 10.9;
+// 4 of 128257, 256 of 2008: 10.3), against 10.3 to 10.9 for the calls of two launches
 static int top2_single_slices(int B, int V) {
     const int two = top2_slices(B, V);
     int nsl = two < 64 ? two : 64;
     while (nsl > 1 && nsl * B > 256) nsl /= 2;
-    return nsl * B <= 256 && nsl * 4 >= two && V <= (V % 4 ? 3072L : 4096L) * nsl ? nsl : 0;
+    if (V % 4 && 21L * nsl * B + V / nsl > 7700) return 0;
+    return nsl * B <= 256 && nsl * 4 >= two && V <= 4096L * nsl ? nsl : 0;
 }
 
 size_t top2_ws_bytes(int B, int V) {

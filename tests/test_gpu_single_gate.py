@@ -14,10 +14,11 @@ from _gpu_common import dev_i32
 
 pytestmark = pytest.mark.gpu
 
-# one row (64 slices), odd and tiny vocabularies, 256 slice states exactly, one slice a row, and
-# (5, 128256), (17, 32064), (200, 8192) past the limit
-SHAPES = [(1, 128256), (1, 2), (2, 5), (3, 1023), (4, 128257), (5, 128256), (16, 32064), (17, 32064), (64, 4096),
-          (65, 4096), (128, 3000), (200, 8192), (256, 40)]
+# one row (64 slices), odd and tiny vocabularies, 256 slice states exactly, one slice a row, halved
+# slices (by the word too), and past the limits: (8, 128257), (9, 128256), (48, 32064) by the slices' length,
+# (200, 8192) by their number
+SHAPES = [(1, 128256), (1, 2), (2, 5), (3, 1023), (4, 128257), (5, 128256), (5, 110001), (8, 128257), (9, 128256),
+          (16, 32064), (17, 32064), (48, 32064), (64, 4096), (65, 4096), (128, 3000), (200, 8192), (256, 40)]
 
 
 def logits(B, V, seed):
